@@ -130,15 +130,30 @@ struct RowShape {
   static constexpr int K = (LOGN2 + RB - 1) / RB;  // rounds
   static constexpr int LAST = LOGN2 - RB * (K - 1);  // stages in the last round
   static constexpr int CHUNK_LDS = K > 1 ? N2 + N2 / 16 : 1;
-  // slot of word tt + u*TPC in the padded chunk (linear in u when TPC % 16 == 0)
-  __device__ __forceinline__ static uint32_t tail_slot(uint32_t tt, uint32_t u) {
-    if constexpr (TPC % 16 == 0) return lds_pad(tt) + u * (TPC + TPC / 16);
-    else return lds_pad(tt + u * TPC);
-  }
   static constexpr int LDS_ELEMS = CPW * CHUNK_LDS;
   // held-bit offset of round j (forward numbering)
   static constexpr int hb(int j) { return j < K - 1 ? LOGN2 - RB - RB * j : 0; }
   static constexpr int nst(int j) { return j < K - 1 ? RB : LAST; }
+  // The LW threads of a chunk that share a wave hold, in every round with at
+  // most 64 words below the held bits, one contiguous block of LW * R words of
+  // the chunk: re-deals between two such rounds stay inside the wave.
+  static constexpr int LW = TPC < 64 ? TPC : 64;
+  static constexpr bool in_wave(int j) { return hb(j) <= 6; }
+  // Word u of thread tt when its wave reads or writes its block contiguously,
+  // and that word's slot (linear in u when LW % 16 == 0).
+  __device__ __forceinline__ static uint32_t tail_word(uint32_t tt) {
+    return (tt / LW) * (LW * R) + tt % LW;
+  }
+  __device__ __forceinline__ static uint32_t tail_slot(uint32_t tt, uint32_t u) {
+    if constexpr (LW % 16 == 0) return lds_pad(tail_word(tt)) + u * (LW + LW / 16);
+    else return lds_pad(tail_word(tt) + u * LW);
+  }
+  // Barriers of a workgroup in the inverse rounds (see lds_exchange).
+  static constexpr int inv_barriers() {
+    int n = 0;
+    for (int j = K - 1; j > 0; --j) n += (in_wave(j) ? 0 : 1) + (in_wave(j) && in_wave(j - 1) ? 0 : 1);
+    return n;
+  }
 };
 
 #define NTT_GLOBAL __attribute__((address_space(1)))
@@ -302,21 +317,42 @@ __device__ __forceinline__ void inv_round_stages(const A& ar, typename A::V (&v)
   }
 }
 
-// Re-deal R values per thread from the layout of round JF to round JT.
-template <class A, int LOGN2, int RB, int JF, int JT>
+// Orders the LDS accesses of one wave's lanes (its LDS instructions execute in
+// order, so this costs no instruction): later accesses stay behind earlier ones.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Re-deal R values per thread from the layout of round JF to round JT (one of
+// them the other's neighbour).  Between two in-wave rounds every slot is written
+// and read by the same wave, so the waves of the workgroup need not meet; only
+// the one or two exchanges that touch a round across waves take barriers: one
+// between the writes and the reads, and one before the writes when other waves
+// may still be reading (JF across waves, and not FIRST: the region's first use
+// since the last barrier).  A 2^12-word radix-16 chunk meets once instead of
+// six times per transform.  What it is worth depends on how few waves there are
+// to hide a barrier behind: forward + inverse of one 56-bit polynomial of 2^15
+// 23.9 -> 21.7 us, a CMux step of 342 ciphertexts 17.4 -> 16.3 us, and nothing
+// on 4 x 36 x 2^16 (58.4 -> 57.9 us), whose two passes run at the copy rate.
+template <class A, int LOGN2, int RB, int JF, int JT, bool FIRST = false>
 __device__ __forceinline__ void lds_exchange(typename A::V (&v)[1 << RB], typename A::V* lds,
                                              uint32_t tt) {
   using S = RowShape<LOGN2, RB>;
   constexpr int HF = S::hb(JF), HT = S::hb(JT);
+  constexpr bool kInWave = S::in_wave(JF) && S::in_wave(JT);
   using MF = LdsMap<RB, HF>;
   using MT = LdsMap<RB, HT>;
   const uint32_t bf = MF::base(tt), bt = MT::base(tt);
+  if constexpr (!FIRST && !S::in_wave(JF)) __syncthreads();
 #pragma unroll
   for (int u = 0; u < S::R; ++u) lds[MF::slot(tt, bf, u)] = v[u];
-  __syncthreads();
+  if constexpr (kInWave) wave_sync();
+  else __syncthreads();
 #pragma unroll
   for (int u = 0; u < S::R; ++u) v[u] = lds[MT::slot(tt, bt, u)];
-  __syncthreads();
+  wave_sync();
 }
 
 template <class A, int LOGN2, int RB, int J>
@@ -331,7 +367,7 @@ __device__ __forceinline__ void row_forward_from(const A& ar, typename A::V (&v)
 #pragma unroll
         for (int u = 0; u < S::R; ++u) ar.center(v[u]);
       }
-      lds_exchange<A, LOGN2, RB, J, J + 1>(v, lds, tt);
+      lds_exchange<A, LOGN2, RB, J, J + 1, (J == 0)>(v, lds, tt);
       row_forward_from<A, LOGN2, RB, J + 1>(ar, v, tw, base, tt, lds);
     }
   }
@@ -410,7 +446,7 @@ __device__ __forceinline__ void row_forward2_from(const A& ar, typename A::V (&v
         }
       }
       // one LDS region: the two re-deals take turns
-      lds_exchange<A, LOGN2, RB, J, J + 1>(va, lds, tt);
+      lds_exchange<A, LOGN2, RB, J, J + 1, (J == 0)>(va, lds, tt);
       lds_exchange<A, LOGN2, RB, J, J + 1>(vb, lds, tt);
       row_forward2_from<A, LOGN2, RB, J + 1>(ar, va, vb, tw, base, tt, lds);
     }
@@ -462,7 +498,8 @@ __device__ __forceinline__ ChunkPos chunk_pos(const RowArgs& a, uint32_t gc, int
 // skipped); `base` = N1 + c is its twiddle base, `tt` the thread's index within
 // the chunk's N2/R threads (R = 2^RB values each), `lds` the chunk's LDS
 // region.  All threads of the workgroup must call it together (it
-// synchronises the workgroup).
+// synchronises the workgroup); it returns while other waves may still be
+// reading `lds`, so a caller that uses the region again synchronises first.
 // INV selects the direction; TWO_PASS says whether a column pass precedes
 // (forward) or follows (inverse): then the pass reads/writes the raw
 // intermediate format instead of canonical words, and the inverse leaves the
@@ -499,37 +536,39 @@ __device__ __forceinline__ void row_chunk(typename A::W* __restrict__ dst,
     row_forward_from<A, LOGN2, RB, 0>(ar, v, tw, base, tt, lds);
     if constexpr (S::K > 1) {
       // The last round holds R consecutive words per thread; re-deal them
-      // through LDS so that each store instruction writes contiguous words.
+      // through the wave's block so that each store writes contiguous words.
       using MB = LdsMap<RB, 0>;
       const uint32_t bb = MB::base(tt);
 #pragma unroll
       for (int u = 0; u < R; ++u) lds[MB::slot(tt, bb, u)] = v[u];
-      __syncthreads();
+      wave_sync();
+      const uint32_t tw0 = S::tail_word(tt);
       if (valid) {
 #pragma unroll
-        for (int u = 0; u < R; ++u) dst[tt + u * S::TPC] = ar.to_word(lds[S::tail_slot(tt, u)]);
+        for (int u = 0; u < R; ++u) dst[tw0 + u * S::LW] = ar.to_word(lds[S::tail_slot(tt, u)]);
       }
-      __syncthreads();
     } else if (valid) {
 #pragma unroll
       for (int u = 0; u < R; ++u) dst[u] = ar.to_word(v[u]);
     }
   } else {
     if constexpr (S::K > 1) {
-      // Contiguous loads into LDS, then each thread takes R consecutive words.
+      // Contiguous loads of the wave's block into LDS, then each thread takes R
+      // consecutive words of it.
+      const uint32_t tw0 = S::tail_word(tt);
 #pragma unroll
       for (int u = 0; u < R; ++u) {
-        const W x = src[tt + u * S::TPC];
+        const W x = src[tw0 + u * S::LW];
         V t = ar.from_word(x);
         ar.center(t);
         lds[S::tail_slot(tt, u)] = t;
       }
-      __syncthreads();
+      wave_sync();
       using MB = LdsMap<RB, 0>;
       const uint32_t bb = MB::base(tt);
 #pragma unroll
       for (int u = 0; u < R; ++u) v[u] = lds[MB::slot(tt, bb, u)];
-      __syncthreads();
+      wave_sync();
     } else {
 #pragma unroll
       for (int u = 0; u < R; ++u) {
@@ -609,7 +648,8 @@ __device__ __forceinline__ void product_inverse(const A& ar, typename A::V (&va)
 
 // The whole fused product on one row chunk (the body of polymul_row_kernel for
 // callers that place chunks themselves): sa, sb and dst point at the chunk
-// (dst may equal sa); `base`, `tt`, `lds` and `valid` as for row_chunk.
+// (dst may equal sa); `base`, `tt`, `lds` and `valid` as for row_chunk, also in
+// leaving `lds` to be synchronised before its next use.
 template <class A, int LOGN2, bool TWO_PASS, int RB = 4>
 __device__ __forceinline__ void polymul_chunk(typename A::W* __restrict__ dst,
                                               const typename A::W* sa, const typename A::W* sb,
@@ -693,12 +733,13 @@ polymul_row_kernel(RowArgs args) {
         const uint32_t bb = MB::base(tt);
 #pragma unroll
         for (int u = 0; u < R; ++u) lds[MB::slot(tt, bb, u)] = x[u];
-        __syncthreads();
+        wave_sync();
+        const uint32_t tw0 = S::tail_word(tt);
         if (cp.valid) {
 #pragma unroll
-          for (int u = 0; u < R; ++u) d[tt + u * S::TPC] = ar.to_word(lds[S::tail_slot(tt, u)]);
+          for (int u = 0; u < R; ++u) d[tw0 + u * S::LW] = ar.to_word(lds[S::tail_slot(tt, u)]);
         }
-        __syncthreads();
+        wave_sync();
       } else if (cp.valid) {
 #pragma unroll
         for (int u = 0; u < R; ++u) d[u] = ar.to_word(x[u]);

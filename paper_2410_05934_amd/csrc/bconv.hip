@@ -61,6 +61,9 @@ struct ntt_bconv_s {
   double* d_f1 = nullptr;    // [L][4]: q_i, 1/q_i, w_i, w_i/q_i
   double* d_f2 = nullptr;    // [L][M][2]: (Q/q_i) mod p_j, that over p_j
   double* d_fp = nullptr;    // [M][2]: p_j, 1/p_j
+  uint32_t few = 0;          // sources the few-source kernel holds in registers (0: not used)
+  double* d_f3 = nullptr;    // [M][2 + 2 few]: p_j, 1/p_j, then per source (Q/q_i) mod p_j and that
+                             // over p_j (zeros past the last source)
   bool mfma = false;         // fp64-eligible, N >= 32, not switched off: int8 MFMA form
   uint64_t* d_kop = nullptr; // MFMA constant operands [ceil(M/4)][ceil(L/2)][64 lanes]
   double* d_om = nullptr;    // [M][8][2]: 256^c mod p_j and that over p_j
@@ -89,6 +92,7 @@ struct BconvArgs {
   const double* f1;
   const double* f2;
   const double* fp;
+  const double* f3;
   const uint64_t* kop;
   const double* om;
   const double* om2;
@@ -240,6 +244,131 @@ __global__ void __launch_bounds__(kBconvBlock) bconv_f64_kernel(BconvArgs a) {
   }
 }
 
+// Exact conversions of integers below 2^52 between words and doubles (through
+// the 2^52 exponent: two operations each way instead of a general conversion).
+__device__ __forceinline__ double small_to_f64(uint64_t x) {
+  return __builtin_bit_cast(double, x | 0x4330000000000000ull) - 4503599627370496.0;
+}
+__device__ __forceinline__ uint64_t f64_to_small(double r) {
+  return __builtin_bit_cast(uint64_t, r + 4503599627370496.0) & 0x000FFFFFFFFFFFFFull;
+}
+// A residue as a double and back: 32-bit words convert in one operation.
+__device__ __forceinline__ double word_to_f64(uint32_t x) { return (double)x; }
+__device__ __forceinline__ double word_to_f64(uint64_t x) { return small_to_f64(x); }
+template <class W>
+__device__ __forceinline__ W f64_to_word(double r) {
+  if constexpr (sizeof(W) == 4) return (W)r;
+  else return f64_to_small(r);
+}
+
+// The fp64 form for few sources (L <= S): every t_i of a coefficient stays in
+// registers, formed once, and the thread walks the targets [y T, (y + 1) T) of its
+// grid row y, kFewUnroll at a time with the loads of their residues (ModDown)
+// ahead of the products.  The form above re-reads and re-forms every t_i for each
+// chunk of 8 targets and leaves a launch of one thread per coefficient with one
+// or two waves per SIMD, all of them waiting on scalar loads.  VALU work is some
+// 7 S + 25 operations per output, below the memory time up to about 10 sources.
+// Measured (ModDown, above form -> this): 36 + 4 limbs of 4 x 2^16 56.7 -> 35.6 us
+// (5.0 TB/s, the copy rate), 24 + 8 53.3 -> 32.6 us, 20 + 5 34.1 -> 21.2 us.
+constexpr int kFewUnroll = 4;
+
+template <class W, int S, int MODE>
+__global__ void __launch_bounds__(kBconvBlock) bconv_few_kernel(BconvArgs a, uint32_t per) {
+  const uint32_t gid = blockIdx.x * kBconvBlock + threadIdx.x;
+  if (gid >= a.total) return;
+  const uint32_t n = gid & ((1u << a.log_n) - 1u);
+  const uint32_t b = gid >> a.log_n;
+  const W* x = static_cast<const W*>(a.in) + (uint64_t)b * a.in_stride + n;
+  W* y = static_cast<W*>(a.out) + (uint64_t)b * a.out_stride + n;
+  const uint32_t j0 = blockIdx.y * per;
+  const uint32_t j1 = j0 + per < a.M ? j0 + per : a.M;
+  W xi[S];
+#pragma unroll
+  for (int i = 0; i < S; ++i) xi[i] = x[(uint64_t)((uint32_t)i < a.L ? i : 0) << a.log_n];
+  double t[S];
+#pragma unroll
+  for (int i = 0; i < S; ++i) {
+    t[i] = 0.0;
+    if ((uint32_t)i < a.L) {
+      const double* f = a.f1 + 4 * i;
+      if (MODE == kBconvUp && j0 == 0)
+        static_cast<W*>(a.copy)[(uint64_t)b * a.aux_stride + ((uint64_t)i << a.log_n) + n] = xi[i];
+      t[i] = f64_mulmod_pre(word_to_f64(xi[i]), f[2], f[3], f[0]);
+      t[i] = t[i] < 0.0 ? t[i] + f[0] : t[i];
+    }
+  }
+  for (uint32_t j = j0; j < j1; j += kFewUnroll) {
+    W xs[kFewUnroll];
+    if (MODE == kBconvDown) {
+#pragma unroll
+      for (int k = 0; k < kFewUnroll; ++k) {
+        const uint32_t jc = j + k < j1 ? j + k : j1 - 1u;
+        xs[k] = static_cast<const W*>(a.sub)[(uint64_t)b * a.aux_stride + ((uint64_t)jc << a.log_n) + n];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kFewUnroll; ++k) {
+      if (j + k < j1) {
+        const double* f = a.f3 + (uint64_t)(j + k) * (2 + 2 * S);
+        const double p = f[0], pinv = f[1];
+        double acc = f64_mulmod_pre(t[0], f[2], f[3], p);
+#pragma unroll
+        for (int i = 1; i < S; ++i) {
+          // eight terms of (-7/8 p, 7/8 p) are summed exactly between centrings
+          if (i % 8 == 0) acc = __builtin_fma(-__builtin_rint(acc * pinv), p, acc);
+          acc += f64_mulmod_pre(t[i], f[2 + 2 * i], f[3 + 2 * i], p);
+        }
+        double r = __builtin_fma(-__builtin_rint(acc * pinv), p, acc);
+        r = r < 0.0 ? r + p : r;
+        r = r >= p ? r - p : r;
+        if (MODE == kBconvDown)
+          r = f64_sub_scale(word_to_f64(xs[k]), r, a.sf[2 * (j + k)], a.sf[2 * (j + k) + 1], p);
+        y[(uint64_t)(j + k) << a.log_n] = f64_to_word<W>(r);
+      }
+    }
+  }
+}
+
+// Grid rows of the few-source kernel: enough to put about eight waves on every
+// SIMD when one coefficient per thread does not, each row at least kFewUnroll
+// targets.  (ModDown 24 + 8 limbs of 4 x 2^16: 37.2 us with four waves, 32.6 with
+// eight, 35.0 with sixteen.)
+inline uint32_t few_rows(uint32_t total, uint32_t M) {
+  const uint32_t want = (uint32_t)((2048ull * 256u + total - 1u) / total);
+  const uint32_t most = (M + kFewUnroll - 1) / kFewUnroll;
+  return want < 1u ? 1u : want < most ? want : most;
+}
+
+template <class W, int S, int MODE>
+static hipError_t launch_few_n(const BconvArgs& a, hipStream_t s) {
+  const uint32_t rows = few_rows(a.total, a.M), per = (a.M + rows - 1) / rows;
+  const dim3 grid((a.total + kBconvBlock - 1) / kBconvBlock, (a.M + per - 1) / per);
+  hipLaunchKernelGGL((bconv_few_kernel<W, S, MODE>), grid, dim3(kBconvBlock), 0, s, a, per);
+  return hipGetLastError();
+}
+
+// Register sizes the few-source kernel is built for.
+inline uint32_t few_size(uint32_t L) { return L <= 8 ? L : L <= 16 ? (L + 1u) & ~1u : 0u; }
+
+template <class W, int MODE>
+static hipError_t launch_few(const BconvArgs& a, uint32_t size, hipStream_t s) {
+  switch (size) {
+    case 1: return launch_few_n<W, 1, MODE>(a, s);
+    case 2: return launch_few_n<W, 2, MODE>(a, s);
+    case 3: return launch_few_n<W, 3, MODE>(a, s);
+    case 4: return launch_few_n<W, 4, MODE>(a, s);
+    case 5: return launch_few_n<W, 5, MODE>(a, s);
+    case 6: return launch_few_n<W, 6, MODE>(a, s);
+    case 7: return launch_few_n<W, 7, MODE>(a, s);
+    case 8: return launch_few_n<W, 8, MODE>(a, s);
+    case 10: return launch_few_n<W, 10, MODE>(a, s);
+    case 12: return launch_few_n<W, 12, MODE>(a, s);
+    case 14: return launch_few_n<W, 14, MODE>(a, s);
+    case 16: return launch_few_n<W, 16, MODE>(a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 typedef int bconv_v16i __attribute__((ext_vector_type(16)));
 constexpr uint64_t kDigitOffset = 0x808080808080ull;  // 128 at digits 0..5
 
@@ -360,15 +489,6 @@ constexpr int kWsMaxTiles = 12;
 constexpr uint32_t kWsMaxLimbs = 48;  // 24 k-steps of constant operands in registers
 constexpr uint32_t kWsHelpers = 4;
 
-// Exact conversions of integers below 2^52 between words and doubles (through
-// the 2^52 exponent: two operations each way instead of a general conversion).
-__device__ __forceinline__ double small_to_f64(uint64_t x) {
-  return __builtin_bit_cast(double, x | 0x4330000000000000ull) - 4503599627370496.0;
-}
-__device__ __forceinline__ uint64_t f64_to_small(double r) {
-  return __builtin_bit_cast(uint64_t, r + 4503599627370496.0) & 0x000FFFFFFFFFFFFFull;
-}
-
 // IPT: coefficient pairs per helper thread (2 * steps * 16 over 256).
 template <class W, int SMAX, int IPT, int MODE>
 __global__ void __launch_bounds__(1024) bconv_ws_kernel(BconvArgs a) {
@@ -416,7 +536,7 @@ __global__ void __launch_bounds__(1024) bconv_ws_kernel(BconvArgs a) {
     };
     // Output J0 + 2h + s (s = 0, 1) is finished by the lanes of half h; its
     // constants stay in registers for the whole launch.
-    double cp[2], cpinv[2], cw[2], cwq[2];
+    double cp[2], cpinv[2], cw[2], cwq[2], cs[2], csq[2];
 #pragma unroll
     for (int sl = 0; sl < 2; ++sl) {
       const uint32_t J = J0 + 2u * h + sl;
@@ -425,9 +545,17 @@ __global__ void __launch_bounds__(1024) bconv_ws_kernel(BconvArgs a) {
       cpinv[sl] = o[1];
       cw[sl] = o[2];
       cwq[sl] = o[3];
+      if (MODE == kBconvDown) {
+        const double* f = a.sf + 2u * (uint64_t)(J < a.M ? J : a.M - 1u);
+        cs[sl] = f[0];
+        csq[sl] = f[1];
+      }
     }
-    // ModDown: the residues x_J of the two outputs this lane finishes, loaded
-    // before the products so that their latency hides behind the MFMA chain.
+    // ModDown: the residues x_J of the two outputs this lane finishes, loaded one
+    // tile ahead and so before the previous tile's stores: loads and stores
+    // complete in order, and a load issued after them would wait for them.  For
+    // the same reason s_J and s_J / p_J are held in registers, not read again per
+    // tile.  36 + 36 limbs of 4 x 2^16: 75 -> 72 us, 16 + 16: 33 -> 28 us.
     auto load_sub = [&](uint32_t tile, W (&xs)[2]) {
       const uint64_t g = (uint64_t)tile * 32u + col;
 #pragma unroll
@@ -467,16 +595,18 @@ __global__ void __launch_bounds__(1024) bconv_ws_kernel(BconvArgs a) {
         const uint32_t J = J0 + 2u * h + sl;
         if (J < a.M) {
           if (MODE == kBconvDown) {
-            r = f64_sub_scale(small_to_f64((uint64_t)xs[sl]), r, a.sf[2 * J], a.sf[2 * J + 1], cp[sl]);
+            r = f64_sub_scale(small_to_f64((uint64_t)xs[sl]), r, cs[sl], csq[sl], cp[sl]);
           }
           static_cast<W*>(a.out)[b * a.out_stride + ((uint64_t)J << a.log_n) + n] = (W)f64_to_small(r);
         }
       }
     };
+    W xn[2] = {0, 0};
+    if (MODE == kBconvDown) load_sub(first, xn);
     __syncthreads();  // the digits of the first two tiles
     for (uint32_t t = 0; first + t < end; ++t) {
-      W xs[2] = {0, 0};
-      if (MODE == kBconvDown) load_sub(first + t, xs);
+      const W xs[2] = {xn[0], xn[1]};
+      if (MODE == kBconvDown) load_sub(first + t + 1u < end ? first + t + 1u : end - 1u, xn);
       finish(products(buffer(t)), first + t, xs);
       __syncthreads();
     }
@@ -589,8 +719,8 @@ static hipError_t launch_ws_ipt(const BconvArgs& a, uint32_t grid, hipStream_t s
 }
 
 template <class W, int MODE>
-static hipError_t launch_bconv_mode(const BconvArgs& a, bool f64, bool mfma, uint32_t ws_grid,
-                                    hipStream_t s) {
+static hipError_t launch_bconv_mode(const BconvArgs& a, bool f64, uint32_t few, bool mfma,
+                                    uint32_t ws_grid, hipStream_t s) {
   static const char* const kNames[3][3] = {{"bconv", "bconv_f64", "bconv_mfma"},
                                            {"modup", "modup_f64", "modup_mfma"},
                                            {"moddown", "moddown_f64", "moddown_mfma"}};
@@ -618,6 +748,7 @@ static hipError_t launch_bconv_mode(const BconvArgs& a, bool f64, bool mfma, uin
   }
   const uint32_t blocks = (uint32_t)(((uint64_t)a.total + kBconvBlock - 1) / kBconvBlock);
   LaunchTimer t(kNames[MODE][f64 ? 1 : 0], cls, (int)a.log_n, false, false, (uint64_t)a.total * a.M, s);
+  if (few) return launch_few<W, MODE>(a, few, s);
   if (f64)
     hipLaunchKernelGGL((bconv_f64_kernel<W, MODE>), dim3(blocks), dim3(kBconvBlock), 0, s, a);
   else
@@ -626,11 +757,11 @@ static hipError_t launch_bconv_mode(const BconvArgs& a, bool f64, bool mfma, uin
 }
 
 template <class W>
-static hipError_t launch_bconv(const BconvArgs& a, int mode, bool f64, bool mfma, uint32_t ws_grid,
-                               hipStream_t s) {
-  if (mode == kBconvUp) return launch_bconv_mode<W, kBconvUp>(a, f64, mfma, ws_grid, s);
-  if (mode == kBconvDown) return launch_bconv_mode<W, kBconvDown>(a, f64, mfma, ws_grid, s);
-  return launch_bconv_mode<W, kBconvPlain>(a, f64, mfma, ws_grid, s);
+static hipError_t launch_bconv(const BconvArgs& a, int mode, bool f64, uint32_t few, bool mfma,
+                               uint32_t ws_grid, hipStream_t s) {
+  if (mode == kBconvUp) return launch_bconv_mode<W, kBconvUp>(a, f64, few, mfma, ws_grid, s);
+  if (mode == kBconvDown) return launch_bconv_mode<W, kBconvDown>(a, f64, few, mfma, ws_grid, s);
+  return launch_bconv_mode<W, kBconvPlain>(a, f64, few, mfma, ws_grid, s);
 }
 
 // Workgroups of the weights-stationary kernel resident per CU (any grid is
@@ -664,6 +795,7 @@ static void free_bconv(ntt_bconv_s* h) {
   if (h->d_f1) (void)hipFree(h->d_f1);
   if (h->d_f2) (void)hipFree(h->d_f2);
   if (h->d_fp) (void)hipFree(h->d_fp);
+  if (h->d_f3) (void)hipFree(h->d_f3);
   if (h->d_kop) (void)hipFree(h->d_kop);
   if (h->d_om) (void)hipFree(h->d_om);
   if (h->d_om2) (void)hipFree(h->d_om2);
@@ -774,11 +906,31 @@ static ntt_status bconv_build(ntt_bconv_s** out, uint32_t N, const uint64_t* src
     if (e == hipSuccess) e = hipMemcpy(h->d_f2, f2.data(), f2.size() * 8, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(h->d_fp, fp.data(), fp.size() * 8, hipMemcpyHostToDevice);
   }
-  // The matrix cores pay off for dense conversions (measured: 36 -> 36 limbs on
-  // one 2^16 polynomial 50 us against 173 us on the vector units); with fewer
-  // than 16 source or target moduli the vector form is faster.
+  // Up to 8 sources the few-source vector form is at the memory rate; from 9 on
+  // its products cost more than the matrix cores' fixed work per output (us,
+  // vector / matrix: ModUp 8 -> 24 limbs of 4 x 2^16 24.0 / 24.7, 12 -> 12
+  // 23.7 / 18.4, 29 -> 10 79.8 / 37.8, 36 -> 1 45.9 / 37.2).  Without constants in
+  // registers (over 48 moduli) the matrix form needs 16 moduli on both sides.
+  const bool ws_shape = L <= kWsMaxLimbs && (M + 3) / 4 <= (uint32_t)kWsMaxTiles &&
+                        !(flags & NTT_BCONV_NO_WS);
   h->mfma = h->f64 && N >= 32 && !(flags & NTT_BCONV_NO_MFMA) &&
-            ((flags & NTT_BCONV_MFMA) || (L >= 16 && M >= 16));
+            ((flags & NTT_BCONV_MFMA) || (ws_shape ? L > 8 : L >= 16 && M >= 16));
+  h->few = h->f64 && !(flags & NTT_BCONV_MFMA) ? few_size(L) : 0u;
+  if (h->few && e == hipSuccess) {
+    const size_t stride = 2 + 2 * (size_t)h->few;
+    std::vector<double> f3(stride * M, 0.0);
+    for (uint32_t j = 0; j < M; ++j) {
+      double* f = f3.data() + stride * j;
+      f[0] = (double)dst_moduli[j];
+      f[1] = 1.0 / (double)dst_moduli[j];
+      for (uint32_t i = 0; i < L; ++i) {
+        f[2 + 2 * i] = (double)c2[2 * ((size_t)i * M + j)];
+        f[3 + 2 * i] = f[2 + 2 * i] * f[1];
+      }
+    }
+    e = hipMalloc(&h->d_f3, f3.size() * 8);
+    if (e == hipSuccess) e = hipMemcpy(h->d_f3, f3.data(), f3.size() * 8, hipMemcpyHostToDevice);
+  }
   if (h->mfma && e == hipSuccess) {
     // Constant operands: for row tile rt (outputs 4 rt .. 4 rt + 3), k-step s
     // (limbs 2s, 2s + 1) and lane l, byte e of the operand is digit c = l mod 8
@@ -824,8 +976,7 @@ static ntt_status bconv_build(ntt_bconv_s** out, uint32_t N, const uint64_t* src
     if (e == hipSuccess) e = hipMemcpy(h->d_kop, kop.data(), kop.size() * 8, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(h->d_om, om.data(), om.size() * 8, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(h->d_om2, om2.data(), om2.size() * 8, hipMemcpyHostToDevice);
-    if (e == hipSuccess && row_tiles <= (uint32_t)kWsMaxTiles && L <= kWsMaxLimbs &&
-        !(flags & NTT_BCONV_NO_WS)) {
+    if (e == hipSuccess && ws_shape) {
       int cus = 0;
       e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device);
       const uint32_t lds = 3u * (2u * steps) * 32u * 8u + 32u * L;
@@ -857,6 +1008,7 @@ static ntt_status bconv_run(const ntt_bconv_s* h, int mode, void* out, uint64_t 
   a.f1 = h->d_f1;
   a.f2 = h->d_f2;
   a.fp = h->d_fp;
+  a.f3 = h->d_f3;
   a.kop = h->d_kop;
   a.om = h->d_om;
   a.om2 = h->d_om2;
@@ -872,12 +1024,19 @@ static ntt_status bconv_run(const ntt_bconv_s* h, int mode, void* out, uint64_t 
   a.sc = sc;
   a.sf = sf;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  // ModDown's extra work per output falls on the few owner waves of the matrix
+  // form: on large calls the vector form stays ahead up to 12 sources (us, vector /
+  // matrix: 29 + 10 limbs of 4 x 2^16 42 / 52, 36 + 12 54 / 57; 29 + 10 of 3 x 2^15
+  // 20 / 17).
+  const bool few_first = !h->mfma || (mode == kBconvDown && h->L <= 12 && a.total >= (1u << 18));
+  const uint32_t few = few_first ? h->few : 0u;
+  const bool mfma = h->mfma && !few;
   // weights-stationary grid: every workgroup that fits at once, at most one per tile
   const uint32_t tiles = a.total >> 5;
   const uint32_t ws_grid = h->ws_grid ? (tiles < h->ws_grid ? tiles : h->ws_grid) : 0u;
   const hipError_t e = h->word_bits == 32
-                           ? launch_bconv<uint32_t>(a, mode, h->f64, h->mfma, ws_grid, s)
-                           : launch_bconv<uint64_t>(a, mode, h->f64, h->mfma, ws_grid, s);
+                           ? launch_bconv<uint32_t>(a, mode, h->f64, few, mfma, ws_grid, s)
+                           : launch_bconv<uint64_t>(a, mode, h->f64, few, mfma, ws_grid, s);
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return NTT_OK;
 }

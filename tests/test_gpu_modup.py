@@ -67,6 +67,45 @@ def test_mod_up_and_down_match_oracle(word_bits, L, K, wide, mfma, logn):
     assert np.array_equal(_down(ext, xw, word_bits), oracle.mod_down(xw, q, p))
 
 
+@pytest.mark.parametrize("word_bits", [32, 64])
+@pytest.mark.parametrize("sources", list(range(1, 17)))
+def test_few_source_conversion_at_every_register_size(word_bits, sources):
+    """Vector form with every t_i in registers: all sizes it is built for and the
+    padded ones between, target counts around its unroll of 4, one grid row and
+    several (N = 2 and 2^12)."""
+    for logn, other in ((1, 1), (12, 4), (12, 13)):
+        N = 1 << logn
+        q, p = _bases(word_bits, sources, other)
+        x = synth.uniform_poly(500 + sources, q, 2, N)
+        up = ntt.BasisExtension(N, q, p, word_bits, mfma=False)
+        assert np.array_equal(_up(up, x, word_bits), oracle.mod_up(x, q, p))
+        conv = ntt.BasisConversion(N, q, p, word_bits, mfma=False)
+        y = empty_device((2, other, N), word_bits)
+        conv(y, to_device(x, word_bits))
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(y, word_bits).astype(np.uint64), oracle.mod_up(x, q, p)[:, sources:])
+        xw = synth.uniform_poly(600 + sources, p + q, 2, N)
+        down = ntt.BasisExtension(N, p, q, word_bits, mfma=False)
+        assert np.array_equal(_down(down, xw, word_bits), oracle.mod_down(xw, p, q))
+
+
+@pytest.mark.parametrize("K", [8, 9, 12, 13])
+def test_large_mod_down_is_the_same_on_both_sides_of_the_rule(K):
+    """2^18 coefficients (where 9 .. 12 sources go to the vector form) and just
+    below, default choice against both forced forms."""
+    q, p = _bases(64, 5, K)
+    for logn, batch in ((16, 4), (15, 7)):
+        N = 1 << logn
+        x = to_device(synth.uniform_poly(700 + K, q + p, batch, N), 64)
+        outs = []
+        for mfma in (None, False, True):
+            out = empty_device((batch, 5, N), 64)
+            ntt.BasisExtension(N, q, p, 64, mfma=mfma).mod_down(out, x)
+            outs.append(out)
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
 def test_mod_down_of_mod_up_times_p():
     """ModDown(P * ModUp-shaped input) through both calls: X = P Y over Q u P is
     exactly Y after ModDown (no fast-conversion error on multiples of P), and

@@ -79,7 +79,7 @@ fused_kernel(FusedArgs args) {
     if (idx >= args.total) break;
     const FusedItem it = fused_item(idx, args.n_tr, args.lag, args.p1, args.p2);
     const uint32_t poly = it.t % args.batch;
-    const uint32_t limb = args.cls_limbs[it.t / args.batch];
+    const uint32_t limb = limb_at(args.cls_limbs, it.t / args.batch);
     W* base = reinterpret_cast<W*>(args.data) + (((uint64_t)poly * args.L + limb) << args.log_n);
     const LimbDev& ld = args.limbs[limb];
     if (it.phase == 1) {
@@ -101,7 +101,7 @@ fused_kernel(FusedArgs args) {
     if (columns) {
       if (it.sub < (1u << LOGN2) / S::BLOCK) {
         const uint32_t col = it.sub * S::BLOCK + threadIdx.x;
-        col_one<A, LOGN1, INV, true>(base + col, base + col, ld, LOGN2, true);
+        col_one<A, LOGN1, INV, true>(base, base, ld, LOGN2, col, true);
       }
     } else if (it.sub < (1u << LOGN1)) {
       W* p = base + ((uint64_t)it.sub << LOGN2);

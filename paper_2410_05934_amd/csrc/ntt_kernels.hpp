@@ -45,12 +45,19 @@ namespace nttk {
 // chunks per 256-thread workgroup).
 constexpr int kRowThreadsMin = 64;
 
+// Limb of entry li of a launch's limb list.  A launch over every limb of the plan
+// (one arithmetic class: the usual case) has no list, so that a workgroup's first
+// loads of data do not wait for a load of its limb index.
+__device__ __forceinline__ uint32_t limb_at(const uint32_t* cls_limbs, uint32_t li) {
+  return cls_limbs ? cls_limbs[li] : li;
+}
+
 struct RowArgs {
   void* dst;                 // output (row pass writes here)
   const void* src;           // input (may equal dst)
   const void* src2;          // second input (fused polymul only)
   const LimbDev* limbs;      // [L]
-  const uint32_t* cls_limbs; // limb indices handled by this launch
+  const uint32_t* cls_limbs; // limb indices handled by this launch (null: all limbs)
   uint32_t n_cls;            // number of entries in cls_limbs
   uint32_t L;                // limbs per polynomial in the data layout
   uint32_t log_n;            // log2 N
@@ -484,7 +491,7 @@ __device__ __forceinline__ ChunkPos chunk_pos(const RowArgs& a, uint32_t gc, int
   const uint32_t rest = g / a.batch;
   const uint32_t c = rest & (n1 - 1);
   const uint32_t li = rest >> a.log_n1;
-  p.limb = ONE ? a.limb0 : a.cls_limbs[li];
+  p.limb = ONE ? a.limb0 : limb_at(a.cls_limbs, li);
   p.off = ((uint64_t)poly * a.L + p.limb) << a.log_n;
   p.off += (uint64_t)c << log_n2;
   p.base = n1 + c;
@@ -760,12 +767,14 @@ polymul_row_kernel(RowArgs args) {
 // workgroup holds 64, 128 or kColBlock columns (the launch chooses).
 constexpr int kColBlock = 256;
 
-// One column of N1 = 2^LOGN1 words at src[k << log_n2], k < N1, written to the
-// same positions of dst.  Runs all of the column's stages in registers.
+// Column r of a limb-row: the N1 = 2^LOGN1 words at src[(k << log_n2) + r], k < N1,
+// written to the same positions of dst.  Runs all of the column's stages in
+// registers.  (The column stays apart from the row pointer: where the caller made
+// the pointers wave-uniform, every access is a scalar base plus one lane offset.)
 template <class A, int LOGN1, bool INV, bool TWO_PASS>
 __device__ __forceinline__ void col_one(typename A::W* __restrict__ dst,
                                         const typename A::W* __restrict__ src, const LimbDev& ld,
-                                        uint32_t log_n2, bool valid) {
+                                        uint32_t log_n2, uint32_t r, bool valid) {
   using V = typename A::V;
   using W = typename A::W;
   using TW = typename A::TW;
@@ -776,7 +785,7 @@ __device__ __forceinline__ void col_one(typename A::W* __restrict__ dst,
     const NTT_GLOBAL TW* tw = gptr(reinterpret_cast<const TW*>(ld.twf));
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
-      const W x = src[(uint64_t)k << log_n2];
+      const W x = (src + ((uint64_t)k << log_n2))[r];
       v[k] = ar.from_word(x);
     }
 #pragma unroll
@@ -798,13 +807,13 @@ __device__ __forceinline__ void col_one(typename A::W* __restrict__ dst,
     if (valid) {
 #pragma unroll
       for (int k = 0; k < N1; ++k)
-        dst[(uint64_t)k << log_n2] = TWO_PASS ? ar.to_raw(v[k]) : ar.to_word(v[k]);
+        (dst + ((uint64_t)k << log_n2))[r] = TWO_PASS ? ar.to_raw(v[k]) : ar.to_word(v[k]);
     }
   } else {
     const NTT_GLOBAL TW* tw = gptr(reinterpret_cast<const TW*>(ld.twi));
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
-      const W x = src[(uint64_t)k << log_n2];
+      const W x = (src + ((uint64_t)k << log_n2))[r];
       v[k] = TWO_PASS ? ar.from_raw(x) : ar.from_word(x);
       ar.center(v[k]);
     }
@@ -832,15 +841,20 @@ __device__ __forceinline__ void col_one(typename A::W* __restrict__ dst,
     }
     if (valid) {
 #pragma unroll
-      for (int k = 0; k < N1; ++k) dst[(uint64_t)k << log_n2] = ar.to_word(v[k]);
+      for (int k = 0; k < N1; ++k) (dst + ((uint64_t)k << log_n2))[r] = ar.to_word(v[k]);
     }
   }
 }
 
 // ONE: the launch's class holds one limb (n_cls == 1), whose index and constants
 // come from the arguments; its twiddles are then wave-uniform loads.
+// UNI: rows of at least 64 words (log_n2 >= 6), so all columns of a wave lie in one
+// limb-row: row, limb and pointers go to scalar registers, and the twiddles and
+// limb constants are scalar loads.  On 36 limbs of 2^16 the 16-word column took 91
+// VGPRs (five waves per SIMD) with per-lane twiddles and takes 64 (eight) so.
 // ROWS: the launch may carry row tables (ColArgs::src_rows and the others).
-template <class A, int LOGN1, bool INV, bool TWO_PASS, bool ONE = false, bool ROWS = false>
+template <class A, int LOGN1, bool INV, bool TWO_PASS, bool ONE = false, bool ROWS = false,
+          bool UNI = false>
 __global__ void __launch_bounds__(kColBlock)
 col_kernel(ColArgs args) {
   using W = typename A::W;
@@ -849,7 +863,10 @@ col_kernel(ColArgs args) {
   const void* src_base = args.src;
   const uint64_t* src_rows = ROWS ? args.src_rows : nullptr;
   const uint64_t* dst_rows = ROWS ? args.dst_rows : nullptr;
-  if ((args.src2 || (ROWS && args.src2_rows)) && gid >= args.total_cols) {
+  // total_cols is a multiple of 64 with UNI, so a wave is on one side of it
+  bool second = (args.src2 || (ROWS && args.src2_rows)) && gid >= args.total_cols;
+  if constexpr (UNI) second = __builtin_amdgcn_readfirstlane((uint32_t)second) != 0;
+  if (second) {
     gid -= args.total_cols;
     dst_base = args.dst2;
     src_base = args.src2;
@@ -860,27 +877,28 @@ col_kernel(ColArgs args) {
   const uint32_t g = valid ? gid : 0;
   const uint32_t n2 = 1u << args.log_n2;
   const uint32_t r = g & (n2 - 1);
-  const uint32_t rest = g >> args.log_n2;
-  // the column's words in its limb-row (poly * L + limb) of src and dst
+  uint32_t rest = g >> args.log_n2;
+  if constexpr (UNI) rest = __builtin_amdgcn_readfirstlane(rest);
+  // limb-row (poly * L + limb) of src and dst
   auto at = [&](uint64_t row, W** d, const W** sp) {
-    *d = reinterpret_cast<W*>(dst_base) + (row << args.log_n) + r;
-    *sp = reinterpret_cast<const W*>(src_base) + (row << args.log_n) + r;
+    *d = reinterpret_cast<W*>(dst_base) + (row << args.log_n);
+    *sp = reinterpret_cast<const W*>(src_base) + (row << args.log_n);
     if constexpr (ROWS) {
-      if (dst_rows) *d = reinterpret_cast<W*>(dst_rows[row]) + r;
-      if (src_rows) *sp = reinterpret_cast<const W*>(src_rows[row]) + r;
+      if (dst_rows) *d = reinterpret_cast<W*>(dst_rows[row]);
+      if (src_rows) *sp = reinterpret_cast<const W*>(src_rows[row]);
     }
   };
   W* d;
   const W* sp;
   if constexpr (ONE) {
     at((uint64_t)rest * args.L + args.limb0, &d, &sp);
-    col_one<A, LOGN1, INV, TWO_PASS>(d, sp, args.one, args.log_n2, valid);
+    col_one<A, LOGN1, INV, TWO_PASS>(d, sp, args.one, args.log_n2, r, valid);
   } else {
     const uint32_t li = rest % args.n_cls;
     const uint32_t poly = rest / args.n_cls;
-    const uint32_t limb = args.cls_limbs[li];
+    const uint32_t limb = limb_at(args.cls_limbs, li);
     at((uint64_t)poly * args.L + limb, &d, &sp);
-    col_one<A, LOGN1, INV, TWO_PASS>(d, sp, args.limbs[limb], args.log_n2, valid);
+    col_one<A, LOGN1, INV, TWO_PASS>(d, sp, args.limbs[limb], args.log_n2, r, valid);
   }
 }
 
@@ -947,7 +965,7 @@ pointwise_kernel(EltArgs args) {
   const uint32_t row = e >> args.log_n;
   const uint32_t li = row % args.n_cls;
   const uint32_t poly = row / args.n_cls;
-  const uint32_t limb = args.cls_limbs[li];
+  const uint32_t limb = limb_at(args.cls_limbs, li);
   const A ar(args.limbs[limb]);
   const uint64_t off = (((uint64_t)poly * args.L + limb) << args.log_n) +
                        (e & ((1u << args.log_n) - 1u));
@@ -979,7 +997,7 @@ mac_kernel(MacArgs args) {
   const uint32_t gc = row / args.n_cls;
   const uint32_t c = gc % args.cols;
   const uint32_t grp = gc / args.cols;
-  const uint32_t limb = args.cls_limbs[li];
+  const uint32_t limb = limb_at(args.cls_limbs, li);
   const A ar(args.limbs[limb]);
   const uint64_t poly_words = (uint64_t)args.L << args.log_n;
   const uint64_t limb_off = ((uint64_t)limb << args.log_n) + (e & ((1u << args.log_n) - 1u));

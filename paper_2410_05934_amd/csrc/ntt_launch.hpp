@@ -52,22 +52,24 @@ hipError_t launch_col_n(const ColArgs& a, hipStream_t s) {
   const uint32_t bs = (a.block == 64 || a.block == 128) ? a.block : (uint32_t)kColBlock;
   const uint32_t blocks = (uint32_t)((threads + bs - 1) / bs);
   LaunchTimer t("col", A::kName, LOGN1, INV, TWO, threads << LOGN1, s);
+  const bool rows = a.src_rows || a.src2_rows || a.dst_rows;
   if constexpr (TWO) {
-    // row tables: built for the two-pass column launches only
-    if (a.src_rows || a.src2_rows || a.dst_rows) {
-      if (a.n_cls == 1)
-        hipLaunchKernelGGL((col_kernel<A, LOGN1, INV, TWO, true, true>), dim3(blocks), dim3(bs), 0, s, a);
-      else
-        hipLaunchKernelGGL((col_kernel<A, LOGN1, INV, TWO, false, true>), dim3(blocks), dim3(bs), 0, s, a);
-      return hipGetLastError();
-    }
+    // rows of at least a wave take the wave-uniform kernels; row tables are built
+    // for the two-pass column launches only
+    const bool uni = a.log_n2 >= 6, one = a.n_cls == 1;
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(bs), 0, s, a); };
+    if (uni && one) rows ? go(col_kernel<A, LOGN1, INV, TWO, true, true, true>)
+                         : go(col_kernel<A, LOGN1, INV, TWO, true, false, true>);
+    else if (uni) rows ? go(col_kernel<A, LOGN1, INV, TWO, false, true, true>)
+                       : go(col_kernel<A, LOGN1, INV, TWO, false, false, true>);
+    else rows ? go(col_kernel<A, LOGN1, INV, TWO, false, true>) : go(col_kernel<A, LOGN1, INV, TWO>);
   } else {
-    if (a.src_rows || a.src2_rows || a.dst_rows) return hipErrorInvalidValue;
+    if (rows) return hipErrorInvalidValue;
+    if (a.n_cls == 1)
+      hipLaunchKernelGGL((col_kernel<A, LOGN1, INV, TWO, true>), dim3(blocks), dim3(bs), 0, s, a);
+    else
+      hipLaunchKernelGGL((col_kernel<A, LOGN1, INV, TWO>), dim3(blocks), dim3(bs), 0, s, a);
   }
-  if (a.n_cls == 1)
-    hipLaunchKernelGGL((col_kernel<A, LOGN1, INV, TWO, true>), dim3(blocks), dim3(bs), 0, s, a);
-  else
-    hipLaunchKernelGGL((col_kernel<A, LOGN1, INV, TWO>), dim3(blocks), dim3(bs), 0, s, a);
   return hipGetLastError();
 }
 
@@ -146,6 +148,11 @@ hipError_t launch_col(int logn1, const ColArgs& a, hipStream_t s) {
   }
 }
 
+// The limbs of class c on the device, or null when they are all of the plan's limbs.
+inline const uint32_t* cls_list(const ntt_plan_s* p, int c) {
+  return p->cls_cnt[c] == p->L ? nullptr : p->d_cls_limbs + p->cls_off[c];
+}
+
 inline RowArgs row_args(const ntt_plan_s* p, int c, void* dst, const void* src, const void* src2,
                         uint32_t batch, int n1 = -1) {
   if (n1 < 0) n1 = (int)p->log_n1;
@@ -154,7 +161,7 @@ inline RowArgs row_args(const ntt_plan_s* p, int c, void* dst, const void* src, 
   a.src = src;
   a.src2 = src2;
   a.limbs = p->d_limbs;
-  a.cls_limbs = p->d_cls_limbs + p->cls_off[c];
+  a.cls_limbs = cls_list(p, c);
   a.n_cls = p->cls_cnt[c];
   a.L = p->L;
   a.log_n = p->log_n;
@@ -174,7 +181,7 @@ inline ColArgs col_args(const ntt_plan_s* p, int c, void* dst, const void* src, 
   a.dst = dst;
   a.src = src;
   a.limbs = p->d_limbs;
-  a.cls_limbs = p->d_cls_limbs + p->cls_off[c];
+  a.cls_limbs = cls_list(p, c);
   a.n_cls = p->cls_cnt[c];
   a.L = p->L;
   a.log_n = p->log_n;
@@ -282,7 +289,7 @@ hipError_t transform_cls(const ntt_plan_s* p, int c, void* data, uint32_t batch,
     FusedArgs fa;
     fa.data = data;
     fa.limbs = p->d_limbs;
-    fa.cls_limbs = p->d_cls_limbs + p->cls_off[c];
+    fa.cls_limbs = cls_list(p, c);
     fa.L = p->L;
     fa.batch = batch;
     fa.log_n = p->log_n;
@@ -326,7 +333,7 @@ hipError_t pointwise_cls(const ntt_plan_s* p, int c, void* out, const void* a,
   ea.a = a;
   ea.b = b;
   ea.limbs = p->d_limbs;
-  ea.cls_limbs = p->d_cls_limbs + p->cls_off[c];
+  ea.cls_limbs = cls_list(p, c);
   ea.n_cls = p->cls_cnt[c];
   ea.L = p->L;
   ea.log_n = p->log_n;
@@ -430,7 +437,7 @@ hipError_t mac_cls(const ntt_plan_s* p, int c, void* out, const void* a, const v
   m.a = a;
   m.key = key;
   m.limbs = p->d_limbs;
-  m.cls_limbs = p->d_cls_limbs + p->cls_off[c];
+  m.cls_limbs = cls_list(p, c);
   m.n_cls = p->cls_cnt[c];
   m.L = p->L;
   m.log_n = p->log_n;
@@ -499,7 +506,7 @@ hipError_t xprod_cls(const ntt_plan_s* p, int c, void* out, const void* a, const
   x.a = a;
   x.key = key;
   x.limbs = p->d_limbs;
-  x.cls_limbs = p->d_cls_limbs + p->cls_off[c];
+  x.cls_limbs = cls_list(p, c);
   x.n_cls = p->cls_cnt[c];
   x.L = p->L;
   x.rows = rows;

@@ -89,7 +89,7 @@ __device__ __noinline__ void ragged_two_pass(const RaggedJobDev* jp, const Ragge
   auto columns = [&]() {
 #pragma unroll 1
     for (uint32_t r = threadIdx.x; r < N2; r += kRaggedBlock)
-      col_one<A, LOGN1, INV, true>(p + r, p + r, ld, LOGN2, true);
+      col_one<A, LOGN1, INV, true>(p, p, ld, LOGN2, r, true);
   };
   auto rows = [&]() {
     // the workgroup's kRaggedBlock threads hold kRaggedBlock / TPC chunks at a time
@@ -157,8 +157,8 @@ __device__ __noinline__ void ragged_polymul_two_pass(const RaggedJobDev* jp, con
   const uint32_t tt = threadIdx.x & (S::TPC - 1);
 #pragma unroll 1
   for (uint32_t r = threadIdx.x; r < N2; r += kRaggedBlock) {
-    col_one<A, LOGN1, false, true>(po + r, pa + r, ld, LOGN2, true);
-    col_one<A, LOGN1, false, true>(pw + r, pb + r, ld, LOGN2, true);
+    col_one<A, LOGN1, false, true>(po, pa, ld, LOGN2, r, true);
+    col_one<A, LOGN1, false, true>(pw, pb, ld, LOGN2, r, true);
   }
   __threadfence_block();
   __syncthreads();
@@ -175,7 +175,7 @@ __device__ __noinline__ void ragged_polymul_two_pass(const RaggedJobDev* jp, con
   __syncthreads();
 #pragma unroll 1
   for (uint32_t r = threadIdx.x; r < N2; r += kRaggedBlock)
-    col_one<A, LOGN1, true, true>(po + r, po + r, ld, LOGN2, true);
+    col_one<A, LOGN1, true, true>(po, po, ld, LOGN2, r, true);
   __threadfence_block();
   __syncthreads();
 }
@@ -316,11 +316,12 @@ __global__ void __launch_bounds__(kColBlock) gang_col_kernel(GangArgs g) {
   const uint32_t gid = blockIdx.x * kColBlock + threadIdx.x;
   const bool valid = gid < (g.n_rows << kGangLogN2);
   const uint32_t x = valid ? gid : 0;
-  const RowRef rr = g.rows[x >> kGangLogN2];
+  // a workgroup's columns lie in one row: its entry is read through scalar registers
+  const RowRef rr = g.rows[__builtin_amdgcn_readfirstlane(x >> kGangLogN2)];
   const uint32_t r = x & ((1u << kGangLogN2) - 1u);
-  W* p = reinterpret_cast<W*>(rr.data) + r;
-  const W* q = g.from_src ? reinterpret_cast<const W*>(rr.src) + r : p;
-  col_one<A, LOGN1, INV, true>(p, q, *rr.ld, kGangLogN2, valid);
+  W* p = reinterpret_cast<W*>(rr.data);
+  const W* q = g.from_src ? reinterpret_cast<const W*>(rr.src) : p;
+  col_one<A, LOGN1, INV, true>(p, q, *rr.ld, kGangLogN2, r, valid);
 }
 
 // Fused product rows of a polymul group: the table holds n_rows product rows

@@ -62,7 +62,7 @@ xprod_kernel(XpArgs args) {
   const uint32_t slot = threadIdx.x / S::TPC;
   const uint32_t tt = threadIdx.x % S::TPC;
   const uint32_t grp = blockIdx.x / args.n_cls;
-  const uint32_t limb = args.cls_limbs[blockIdx.x % args.n_cls];
+  const uint32_t limb = limb_at(args.cls_limbs, blockIdx.x % args.n_cls);
   const LimbDev& ld = args.limbs[limb];
   const A ar(ld);
   const uint64_t poly_words = (uint64_t)args.L << LOGN2;

@@ -115,19 +115,33 @@ NTT_HD uint64_t shoup_mul(uint64_t y, uint64_t w, uint64_t ws, uint64_t q) {
   return y * w - mulhi64(y, ws) * q;
 }
 
+// Low 64 bits of (hi 2^64 + lo) >> s, s = 0 .. 63, on the device from 32-bit funnel
+// shifts: a 64-bit vector shift whose amount sits in the highest register of the
+// wave's allocation gave wrong words on gfx950 once several workgroups shared a
+// compute unit (a pointwise kernel with the amount in v39 of 40 registers), and
+// which register the compiler picks cannot be chosen here.
+NTT_HD uint64_t shr128(uint64_t lo, uint64_t hi, uint32_t s) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const uint32_t w0 = (uint32_t)lo, w1 = (uint32_t)(lo >> 32), w2 = (uint32_t)hi, w3 = (uint32_t)(hi >> 32);
+  const bool up = s >= 32;
+  const uint32_t x0 = up ? w1 : w0, x1 = up ? w2 : w1, x2 = up ? w3 : w2;
+  return ((uint64_t)__builtin_amdgcn_alignbit(x2, x1, s) << 32) | __builtin_amdgcn_alignbit(x1, x0, s);
+#else
+  return s ? (lo >> s) | (hi << (64 - s)) : lo;
+#endif
+}
+
 // Barrett-style product of two operands in [0, q), q < 2^62, b = bit length
 // of q, mu = floor(2^(2b) / q).  Result in [0, q).
 NTT_HD uint64_t barrett_mul(uint64_t a, uint64_t b, uint64_t q, uint64_t mu, uint32_t qbits) {
   const uint64_t lo = a * b;
   const uint64_t hi = mulhi64(a, b);
   // t = floor(P / 2^(qbits-1)) < 2^(qbits+1)
-  const uint32_t s1 = qbits - 1;
-  const uint64_t t = (lo >> s1) | (hi << (64 - s1));
+  const uint64_t t = shr128(lo, hi, qbits - 1);
   // e = floor(t * mu / 2^(qbits+1))
   const uint64_t plo = t * mu;
   const uint64_t phi = mulhi64(t, mu);
-  const uint32_t s2 = qbits + 1;
-  const uint64_t e = (plo >> s2) | (phi << (64 - s2));
+  const uint64_t e = shr128(plo, phi, qbits + 1);
   uint64_t r = lo - e * q;  // in [0, 3q)
   r = r >= q ? r - q : r;
   r = r >= q ? r - q : r;
@@ -190,7 +204,15 @@ struct ArF64S {
   NTT_HD V mul(V x, V y) const {
     return f64_mulmod2(f64_center(x, q, qinv), f64_center(y, q, qinv), q, qinv);
   }
-  NTT_HD V add(V x, V y) const { return f64_center(x + y, q, qinv); }
+  // Multiply-accumulate: a transform's value as an operand, its product with a
+  // canonical word, the sum of up to eight products on a folded sum, the fold.
+  // Any |f| < 2^12 q and 2^20 terms stay far below 2^53: nothing to reduce.
+  NTT_HD V mac_operand(V x) const { return x; }
+  NTT_HD V mac_term(V f, V k) const { return f64_mulmod(f, k, q, qinv); }
+  NTT_HD V mac_add(V a, V t) const { return a + t; }
+  NTT_HD V mac_fold(V a) const { return f64_center(a, q, qinv); }
+  // A gadget digit (|d| <= 2^31; top digits are not negative) as a value.
+  NTT_HD V from_digit(uint32_t d, bool top) const { return top ? (double)d : (double)(int32_t)d; }
 };
 
 struct ArF64L {
@@ -231,7 +253,15 @@ struct ArF64L {
   NTT_HD V mul(V x, V y) const {
     return f64_mulmod2(f64_center(x, q, qinv), f64_center(y, q, qinv), q, qinv);
   }
-  NTT_HD V add(V x, V y) const { return f64_center(x + y, q, qinv); }
+  // Multiply-accumulate: a transform's value as an operand, its product with a
+  // canonical word, the sum of up to eight products on a folded sum, the fold.
+  // |f| <= q (centred, or a canonical word) and k in [0, q): |term| <= 7/8 q, and
+  // q/2 + 2 plus eight of them stay below 2^53.
+  NTT_HD V mac_operand(V x) const { return f64_center(x, q, qinv); }
+  NTT_HD V mac_term(V f, V k) const { return f64_mulmod(f, k, q, qinv); }
+  NTT_HD V mac_add(V a, V t) const { return a + t; }
+  NTT_HD V mac_fold(V a) const { return f64_center(a, q, qinv); }
+  NTT_HD V from_digit(uint32_t d, bool top) const { return top ? (double)d : (double)(int32_t)d; }
 };
 
 struct ArI64 {
@@ -279,6 +309,14 @@ struct ArI64 {
   NTT_HD V add(V x, V y) const {
     const uint64_t s = x + y;
     return s >= q ? s - q : s;
+  }
+  // Multiply-accumulate on canonical values.
+  NTT_HD V mac_operand(V x) const { return to_word(x); }
+  NTT_HD V mac_term(V f, V k) const { return barrett_mul(f, k, q, mu, qbits); }
+  NTT_HD V mac_add(V a, V t) const { return add(a, t); }
+  NTT_HD V mac_fold(V a) const { return a; }
+  NTT_HD V from_digit(uint32_t d, bool top) const {
+    return top || !(d >> 31) ? (V)d : q - (V)(0u - d);
   }
 };
 

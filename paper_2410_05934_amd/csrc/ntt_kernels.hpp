@@ -973,26 +973,32 @@ pointwise_kernel(EltArgs args) {
   load_words<W, VEC>(x, reinterpret_cast<const W*>(args.a) + off);
   load_words<W, VEC>(y, reinterpret_cast<const W*>(args.b) + off);
 #pragma unroll
-  for (int k = 0; k < VEC; ++k) z[k] = ar.to_word(ar.mul(ar.from_word(x[k]), ar.from_word(y[k])));
+  for (int k = 0; k < VEC; ++k) z[k] = ar.to_word(ar.mac_term(ar.from_word(x[k]), ar.from_word(y[k])));
   store_words<W, VEC>(reinterpret_cast<W*>(args.dst) + off, z);
 }
 
 // Grouped multiply-accumulate (external-product MAC in the NTT domain):
 // out[g][c] = sum over rows r present in group g of a[g*rows + r] (.) key[r][c].
 // One thread per VEC consecutive words of one (group, column, limb) row.  Rows
-// are taken kMacRows at a time with every load issued before the products (the
-// rows beyond the group's end are computed and dropped by a select, so no
-// branch holds a load back).
+// are taken kMacRows at a time with every load issued before the products.  UNI:
+// N / VEC is at least 64, so a wave's words lie in one row: group, column, limb and
+// pointers are scalar and the rows beyond the group's end are skipped by a scalar
+// branch; else they are computed and dropped by a select, so that no branch holds
+// a load back.  The operands are canonical words, so the fp64 classes need neither
+// side centred and add up to eight products before a fold: 7 operations a product
+// instead of 13 (2048 operands of 2^10, rows = 6, cols = 2: 8.4 -> 5.7 us for
+// 11 MB; what is left is one short wave of workgroups).
 constexpr int kMacRows = 8;
 
-template <class A, int VEC>
+template <class A, int VEC, bool UNI>
 __global__ void __launch_bounds__(kEltBlock)
 mac_kernel(MacArgs args) {
   using W = typename A::W;
   using V = typename A::V;
   const uint32_t e = (blockIdx.x * kEltBlock + threadIdx.x) * VEC;
   if (e >= args.total) return;
-  const uint32_t row = e >> args.log_n;  // (group * cols + c) * n_cls + li
+  uint32_t row = e >> args.log_n;  // (group * cols + c) * n_cls + li
+  if constexpr (UNI) row = __builtin_amdgcn_readfirstlane(row);
   const uint32_t li = row % args.n_cls;
   const uint32_t gc = row / args.n_cls;
   const uint32_t c = gc % args.cols;
@@ -1000,35 +1006,41 @@ mac_kernel(MacArgs args) {
   const uint32_t limb = limb_at(args.cls_limbs, li);
   const A ar(args.limbs[limb]);
   const uint64_t poly_words = (uint64_t)args.L << args.log_n;
-  const uint64_t limb_off = ((uint64_t)limb << args.log_n) + (e & ((1u << args.log_n) - 1u));
+  const uint64_t limb_off = (uint64_t)limb << args.log_n;
+  const uint32_t n = e & ((1u << args.log_n) - 1u);
   const uint32_t first = grp * args.rows;
   const uint32_t nr = min(args.rows, args.num_operands - first);
-  const W* a = reinterpret_cast<const W*>(args.a);
-  const W* key = reinterpret_cast<const W*>(args.key);
+  const W* a = reinterpret_cast<const W*>(args.a) + limb_off;
+  const W* key = reinterpret_cast<const W*>(args.key) + limb_off;
   V acc[VEC];
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) acc[v] = V{};
   for (uint32_t r0 = 0; r0 < nr; r0 += kMacRows) {
     W x[kMacRows][VEC], k[kMacRows][VEC];
 #pragma unroll
     for (int i = 0; i < kMacRows; ++i) {
+      if (UNI && r0 + i >= nr) break;
       const uint32_t r = r0 + i < nr ? r0 + i : r0;  // in range; dropped below
-      load_words<W, VEC>(x[i], a + (uint64_t)(first + r) * poly_words + limb_off);
-      load_words<W, VEC>(k[i], key + ((uint64_t)r * args.cols + c) * poly_words + limb_off);
+      load_words<W, VEC>(x[i], a + (uint64_t)(first + r) * poly_words + n);
+      load_words<W, VEC>(k[i], key + ((uint64_t)r * args.cols + c) * poly_words + n);
     }
     __builtin_amdgcn_sched_barrier(0);  // keep every load above the products
 #pragma unroll
     for (int i = 0; i < kMacRows; ++i) {
+      if (UNI && r0 + i >= nr) break;
 #pragma unroll
       for (int v = 0; v < VEC; ++v) {
-        const V prod = ar.mul(ar.from_word(x[i][v]), ar.from_word(k[i][v]));
-        const V sum = (r0 + i == 0) ? prod : ar.add(acc[v], prod);
-        acc[v] = (r0 + i < nr) ? sum : acc[v];
+        const V sum = ar.mac_add(acc[v], ar.mac_term(ar.from_word(x[i][v]), ar.from_word(k[i][v])));
+        acc[v] = (UNI || r0 + i < nr) ? sum : acc[v];
       }
     }
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[v] = ar.mac_fold(acc[v]);
   }
   W z[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) z[v] = ar.to_word(acc[v]);
-  store_words<W, VEC>(reinterpret_cast<W*>(args.dst) + (uint64_t)gc * poly_words + limb_off, z);
+  store_words<W, VEC>(reinterpret_cast<W*>(args.dst) + (uint64_t)gc * poly_words + limb_off + n, z);
 }
 
 }  // namespace nttk

@@ -452,8 +452,12 @@ hipError_t mac_cls(const ntt_plan_s* p, int c, void* out, const void* a, const v
   const int per = vec ? kVec : 1;
   const uint32_t blocks = (uint32_t)((m.total / per + kEltBlock - 1) / kEltBlock);
   LaunchTimer t("mac", A::kName, p->log_n, false, false, m.total, s);
-  if (vec) hipLaunchKernelGGL((mac_kernel<A, kVec>), dim3(blocks), dim3(kEltBlock), 0, s, m);
-  else hipLaunchKernelGGL((mac_kernel<A, 1>), dim3(blocks), dim3(kEltBlock), 0, s, m);
+  if (vec && p->N / kVec >= 64)
+    hipLaunchKernelGGL((mac_kernel<A, kVec, true>), dim3(blocks), dim3(kEltBlock), 0, s, m);
+  else if (vec)
+    hipLaunchKernelGGL((mac_kernel<A, kVec, false>), dim3(blocks), dim3(kEltBlock), 0, s, m);
+  else
+    hipLaunchKernelGGL((mac_kernel<A, 1, false>), dim3(blocks), dim3(kEltBlock), 0, s, m);
   return hipGetLastError();
 }
 

@@ -46,6 +46,10 @@ enum XpMode : int {
 // cols <= rows.
 // kXpDecompose: the operands are not in memory; slot s = c * levels + j computes
 // digit j of component c of ciphertext `grp` as it loads (Decompose, fused).
+// A digit goes into the transform as the small signed number it is (its residue mod
+// q gives the same words); the products take F as the forward leaves it (32-bit
+// moduli) or centred once when it is published, and are folded every eight rows.
+// CMux step of 342 ciphertexts at 2^10: 16.0 -> 15.3 us.
 // kXpCmux: one CMux of blind rotation (Sec. II-B, Sec. IV-A): the digits are
 // those of X^r acc - acc (r = rot[grp]), and the stored result is acc plus the
 // inverse transform, i.e. acc + ExtProd(key, X^r acc - acc); cols = comps.
@@ -95,37 +99,35 @@ xprod_kernel(XpArgs args) {
   // transforms the group's first operand and its result is never read).
   const uint32_t op = slot < nr ? slot : 0;
   V v[R];
-  if constexpr (MODE == kXpDecompose) {
+  if constexpr (MODE == kXpDecompose || MODE == kXpCmux) {
     const uint32_t comp = op / args.levels;
     const uint32_t digit = op - comp * args.levels;
+    const bool top = digit + 1 >= args.levels;
     const W* src = reinterpret_cast<const W*>(args.a) +
                    ((uint64_t)grp * args.comps + comp) * poly_words + limb_off;
+    if constexpr (MODE == kXpDecompose) {
 #pragma unroll
-    for (int u = 0; u < R; ++u)
-      v[u] = ar.from_word(signed_digit<W>(src[ins_bits<RB>(tt, u, H0)], digit, args.levels,
-                                          args.log_base, args.dec_offset, ld.q));
-  } else if constexpr (MODE == kXpCmux) {
-    const uint32_t comp = op / args.levels;
-    const uint32_t digit = op - comp * args.levels;
-    const W* src = reinterpret_cast<const W*>(args.a) +
-                   ((uint64_t)grp * args.comps + comp) * poly_words + limb_off;
-    constexpr uint32_t kN = 1u << LOGN2;
-    // X^r = -X^(r - N) for r >= N; then coefficient pos of X^r' a is a[pos - r'],
-    // negated once more when pos - r' wraps below zero.
-    uint32_t r = args.rot[grp] & (2u * kN - 1u);
-    const bool flip = r >= kN;
-    r &= kN - 1u;
-    const uint64_t q = ld.q;
+      for (int u = 0; u < R; ++u)
+        v[u] = ar.from_digit(digit_bits(src[ins_bits<RB>(tt, u, H0)], digit, top, args.log_base,
+                                        args.dec_offset), top);
+    } else {
+      constexpr uint32_t kN = 1u << LOGN2;
+      // X^r = -X^(r - N) for r >= N; then coefficient pos of X^r' a is a[pos - r'],
+      // negated once more when pos - r' wraps below zero.
+      uint32_t r = args.rot[grp] & (2u * kN - 1u);
+      const bool flip = r >= kN;
+      r &= kN - 1u;
+      const W q = (W)ld.q;
 #pragma unroll
-    for (int u = 0; u < R; ++u) {
-      const uint32_t pos = ins_bits<RB>(tt, u, H0);
-      const bool wrap = pos < r;
-      const uint64_t rv = (uint64_t)src[(pos - r) & (kN - 1u)];
-      const uint64_t av = (uint64_t)src[pos];
-      const uint64_t sv = (flip != wrap) ? (rv == 0 ? 0 : q - rv) : rv;  // X^r acc at pos
-      const uint64_t dv = sv >= av ? sv - av : sv + q - av;             // minus acc
-      v[u] = ar.from_word(signed_digit<W>((W)dv, digit, args.levels, args.log_base,
-                                          args.dec_offset, q));
+      for (int u = 0; u < R; ++u) {
+        const uint32_t pos = ins_bits<RB>(tt, u, H0);
+        const bool wrap = pos < r;
+        const W rv = src[(pos - r) & (kN - 1u)];
+        const W av = src[pos];
+        const W sv = (flip != wrap && rv != 0) ? (W)(q - rv) : rv;  // X^r acc at pos
+        const W dv = sv >= av ? (W)(sv - av) : (W)(sv - av + q);    // minus acc, mod 2^bits
+        v[u] = ar.from_digit(digit_bits(dv, digit, top, args.log_base, args.dec_offset), top);
+      }
     }
   } else {
     const W* src = reinterpret_cast<const W*>(args.a) + (uint64_t)(first + op) * poly_words +
@@ -137,12 +139,12 @@ xprod_kernel(XpArgs args) {
   const typename A::TW* twf = uniform_ptr(reinterpret_cast<const typename A::TW*>(ld.twf));
   const typename A::TW* twi = uniform_ptr(reinterpret_cast<const typename A::TW*>(ld.twi));
   row_forward_from<A, LOGN2, RB, 0>(ar, v, twf, 1u, tt, lds);
-  // Publish F_slot: thread tt holds positions tt*R + u (the last round's layout,
+  // Publish F_slot, ready for the products: thread tt holds positions tt*R + u (the last round's layout,
   // in its wave's own block of the region).
   using MB = LdsMap<RB, 0>;
   const uint32_t bb = MB::base(tt);
 #pragma unroll
-  for (int u = 0; u < R; ++u) lds[MB::slot(tt, bb, u)] = v[u];
+  for (int u = 0; u < R; ++u) lds[MB::slot(tt, bb, u)] = ar.mac_operand(v[u]);
   __syncthreads();
 
   // acc = sum over the group's rows of F_r (.) key[r][c].  When a slot spans
@@ -160,14 +162,14 @@ xprod_kernel(XpArgs args) {
     const V* fr = lds_all + r * kRegion;
 #pragma unroll
     for (int u = 0; u < R; ++u) {
-      const V prod = ar.mul(fr[MB::slot(tt, bb, u)], ar.from_word(kcur[u]));
-      acc[u] = r == 0 ? prod : ar.add(acc[u], prod);
+      acc[u] = ar.mac_add(acc[u], ar.mac_term(fr[MB::slot(tt, bb, u)], ar.from_word(kcur[u])));
+      if ((r & 7u) == 7u) acc[u] = ar.mac_fold(acc[u]);
     }
 #pragma unroll
     for (int u = 0; u < R; ++u) kcur[u] = knext[u];
   }
 #pragma unroll
-  for (int u = 0; u < R; ++u) ar.center(acc[u]);
+  for (int u = 0; u < R; ++u) acc[u] = ar.mac_fold(acc[u]);
   __syncthreads();  // every slot has read the F regions before they are reused
 
   // Inverse transform of the accumulator; only the first `cols` slots store.

@@ -482,10 +482,20 @@ def find_root(N: int, q: int) -> int:
     return int(out.value)
 
 
+_current_raw = None  # handle of the calling thread's current stream on a device
+
+
 def _stream_handle(stream) -> int:
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # Looked up on every call, as a bare handle: building a torch.cuda.Stream for it
+    # took 2.9 of the 7.2 us of a small call (0.2 us so).
+    global _current_raw
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if _current_raw is None:
+        _current_raw = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+            (lambda device: torch.cuda.current_stream(device).cuda_stream)
+    return int(_current_raw(torch.cuda.current_device()))
 
 
 class Plan:

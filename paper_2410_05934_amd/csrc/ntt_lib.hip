@@ -109,8 +109,13 @@ static ntt_status build_plan(ntt_plan_s* p, const uint64_t* moduli) {
     LimbDev& d = limbs[l];
     std::memset(&d, 0, sizeof(d));
     d.q = q;
-    d.qd = (double)q;
-    d.qinv = 1.0 / (double)q;
+    if (c == 2) {
+      d.nq = 0 - q;
+      d.nq2 = 0 - 2 * q;
+    } else {
+      d.qd = (double)q;
+      d.qinv = 1.0 / (double)q;
+    }
     d.cls = c;
     d.qbits = 64 - __builtin_clzll(q);
     d.bmu = (uint64_t)(((u128)1 << (2 * d.qbits)) / q);

@@ -329,6 +329,16 @@ ntt_status ntt_forward_mul(ntt_plan_t plan, void* out, void* a, void* b, uint32_
 ntt_status ntt_polymul(ntt_plan_t plan, void* out, const void* a, const void* b, uint32_t batch,
                        void* stream);
 
+/* ntt_polymul with the two-pass workspace from the caller: *bytes of
+ * ntt_polymul_workspace (0 for a single-pass product) at ws, device memory that
+ * nothing else uses until the stream has passed the call.  The pool allocation
+ * and release of ntt_polymul cost the host some 15 us a call; a caller with an
+ * allocator of its own (the Python binding) passes a block here.  With ws null or
+ * too small the call allocates as ntt_polymul does. */
+ntt_status ntt_polymul_workspace(ntt_plan_t plan, uint32_t batch, uint64_t* bytes);
+ntt_status ntt_polymul_ws(ntt_plan_t plan, void* out, const void* a, const void* b, uint32_t batch,
+                          void* ws, uint64_t ws_bytes, void* stream);
+
 /* ntt_polymul for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same arguments, kernels and words, but the two-pass workspace comes from a

@@ -73,6 +73,8 @@ _SIGS = {
     "ntt_pointwise_mac": [_vp, _vp, _vp, _vp, _u32, _u32, _u32, _u32, _vp],
     "ntt_external_product": [_vp, _vp, _vp, _vp, _u32, _u32, _u32, _vp],
     "ntt_polymul": [_vp, _vp, _vp, _vp, _u32, _vp],
+    "ntt_polymul_workspace": [_vp, _u32, ctypes.POINTER(_u64)],
+    "ntt_polymul_ws": [_vp, _vp, _vp, _vp, _u32, _vp, _u64, _vp],
     "ntt_polymul_noalloc": [_vp, _vp, _vp, _vp, _u32, _vp],
     "ntt_automorph": [_vp, _vp, _vp, _u32, _u32, _u32, _vp],
     "ntt_forward_mul": [_vp, _vp, _vp, _vp, _u32, _vp],
@@ -498,6 +500,21 @@ def _stream_handle(stream) -> int:
     return int(_current_raw(torch.cuda.current_device()))
 
 
+def _workspace(nbytes: int, device, stream):
+    """Scratch that torch's allocator hands out on the call's stream (its memory is
+    reused only in that stream's order), or None: under graph capture or out of memory."""
+    import torch
+    try:
+        if stream is not None:
+            with torch.cuda.stream(stream):
+                return _workspace(nbytes, device, None)
+        if torch.cuda.is_current_stream_capturing():
+            return None
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 class Plan:
     """An NTT plan: length N, RNS moduli, word width; owns device twiddle tables.
 
@@ -680,8 +697,17 @@ class Plan:
         n = self._batch_of(out, "out")
         if self._batch_of(a, "a") != n or self._batch_of(b, "b") != n:
             raise ValueError("batch mismatch")
-        _check(lib().ntt_polymul(self._h, out.data_ptr(), a.data_ptr(), b.data_ptr(), n,
-                                 _stream_handle(stream)), "ntt_polymul")
+        # The two-pass workspace comes from torch's allocator, taken and given back
+        # on the stream of the call, not from a pool allocation inside the library
+        # (15 us of host time); under capture, or when torch has no room, the library
+        # allocates it.
+        need = _u64()
+        if self.N > 4096:  # shorter products take one pass
+            _check(lib().ntt_polymul_workspace(self._h, n, ctypes.byref(need)), "ntt_polymul")
+        ws = _workspace(need.value, out.device, stream) if need.value else None
+        _check(lib().ntt_polymul_ws(self._h, out.data_ptr(), a.data_ptr(), b.data_ptr(), n,
+                                    None if ws is None else ws.data_ptr(), need.value,
+                                    _stream_handle(stream)), "ntt_polymul")
         return out
 
     def polymul_noalloc(self, out, a, b, stream=None):

@@ -795,8 +795,17 @@ ntt_status ntt_forward_mul(ntt_plan_t plan, void* out, void* a, void* b, uint32_
   return NTT_OK;
 }
 
-ntt_status ntt_polymul(ntt_plan_t plan, void* out, const void* a, const void* b, uint32_t batch,
-                       void* stream) {
+ntt_status ntt_polymul_workspace(ntt_plan_t plan, uint32_t batch, uint64_t* bytes) {
+  clear_error();
+  const ntt_status st = check_plan_batch(plan, batch);
+  if (st != NTT_OK) return st;
+  if (!bytes) return fail(NTT_EINVAL, "null bytes");
+  *bytes = polymul_ws_bytes(plan, batch);
+  return NTT_OK;
+}
+
+ntt_status ntt_polymul_ws(ntt_plan_t plan, void* out, const void* a, const void* b, uint32_t batch,
+                          void* ws, uint64_t ws_bytes, void* stream) {
   clear_error();
   ntt_status st = check_plan_batch(plan, batch);
   if (st != NTT_OK) return st;
@@ -805,15 +814,19 @@ ntt_status ntt_polymul(ntt_plan_t plan, void* out, const void* a, const void* b,
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = validate_words(plan, a, batch, s, "a")) != NTT_OK) return st;
   if ((st = validate_words(plan, b, batch, s, "b")) != NTT_OK) return st;
-  void* ws = nullptr;
   const size_t bytes = polymul_ws_bytes(plan, batch);
-  if (bytes) {
-    hipError_t e = hipMallocAsync(&ws, bytes, s);
-    if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(polymul workspace)");
-  }
-  const ntt_status rc = polymul_into(plan, out, a, b, batch, ws, s);
-  if (ws) (void)hipFreeAsync(ws, s);
+  if (!bytes || (ws && ws_bytes >= bytes)) return polymul_into(plan, out, a, b, batch, ws, s);
+  void* own = nullptr;
+  hipError_t e = hipMallocAsync(&own, bytes, s);
+  if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(polymul workspace)");
+  const ntt_status rc = polymul_into(plan, out, a, b, batch, own, s);
+  (void)hipFreeAsync(own, s);
   return rc;
+}
+
+ntt_status ntt_polymul(ntt_plan_t plan, void* out, const void* a, const void* b, uint32_t batch,
+                       void* stream) {
+  return ntt_polymul_ws(plan, out, a, b, batch, nullptr, 0, stream);
 }
 
 }  // extern "C"

@@ -1,0 +1,44 @@
+"""GPU: a product whose workspace the caller brings."""
+import ctypes
+
+import pytest
+
+from paper_2410_05934_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2410_05934_amd as ntt  # noqa: E402
+
+
+def test_product_workspace_from_the_caller():
+    """Too small or missing: the library allocates its own; large enough: used."""
+    mods = synth.primes_below(1 << 50, 1 << 17, 2)
+    N = 1 << 15
+    plan = ntt.Plan(N, mods, 64)
+    a = torch.randint(0, mods[-1], (2, 2, N), device="cuda")
+    b = torch.randint(0, mods[-1], (2, 2, N), device="cuda")
+    want = torch.empty_like(a)
+    plan.polymul(want, a, b)
+    need = ctypes.c_uint64()
+    assert ntt.lib().ntt_polymul_workspace(plan._h, 2, ctypes.byref(need)) == 0
+    assert need.value == a.numel() * 8
+    ws = torch.full((a.numel() + 16,), -1, dtype=torch.int64, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    for ptr, size in ((None, 0), (ws.data_ptr(), need.value - 8), (ws.data_ptr(), need.value)):
+        out = torch.empty_like(a)
+        assert ntt.lib().ntt_polymul_ws(plan._h, out.data_ptr(), a.data_ptr(), b.data_ptr(), 2, ptr,
+                                        size, stream) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert bool((ws[a.numel():] == -1).all())
+        assert bool((ws[:a.numel()] == -1).all()) == (size < need.value)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    out = torch.empty_like(a)
+    plan.polymul(out, a, b, stream=side)
+    side.synchronize()
+    assert torch.equal(out, want)

@@ -31,6 +31,7 @@ struct ntt_plan_s {
   int device = 0;
   uint32_t N = 0, log_n = 0, L = 0, word_bits = 0, flags = 0;
   uint32_t log_n1 = 0;                // default column stages (0: single pass)
+  bool size_split = false;            // splits may follow the size of a call (no flag fixes rows)
   int forced_split = -1;              // NTT_FLAG_SPLIT, or -1
   int row_rb = 0;                     // forced log2 values per thread in row passes (0: choose)
   uint32_t col_block = 0;             // forced column-pass workgroup size (0: choose)
@@ -57,8 +58,27 @@ inline uint32_t polymul_split_log(uint32_t log_n, uint32_t n1) {
   if (n1 == 0) return log_n <= 13 ? 0u : log_n - 13;
   return (log_n > 13 && log_n - n1 > 13) ? log_n - 13 : n1;
 }
-inline uint32_t polymul_split(const ntt_plan_s* p, uint32_t n1) {
-  return polymul_split_log(p->log_n, n1);
+
+// Column stages of a plan's transforms with rows of 2^12 words: what the flags that
+// name a row form (single launch, radix-8, radix-4) were defined for.
+inline uint32_t split_4096(uint32_t log_n) {
+  return log_n < 4 ? log_n : log_n <= 12 ? 0u : log_n - 12;
+}
+// Default column stages by arithmetic class.  Measured (forward / inverse, us):
+//   fp64 classes: N = 2^13 in one pass saves the second trip through memory at any
+//   batch (32 limb-rows 9 / 9 against 12 / 11 with 2^12-word rows, 144: 10 / 10
+//   against 17 / 17, 324: 17 / 18 against 22 / 27); N = 2^15 with 2^11-word rows
+//   (36 limb-rows 17 / 17 against 18 / 19).
+//   64-bit integers: 2^11-word rows up to N = 2^15 (144 limb-rows of 2^14: 25 / 32
+//   against 29 / 33; of 2^15 42 / 45 against 44 / 45), since its long butterflies
+//   want more threads per transform; one pass at 2^13 is slower for few rows (3: 14
+//   against 11).
+//   N = 2^16 keeps 2^12-word rows: a 32-word column is too wide for the registers.
+inline uint32_t default_split(uint32_t log_n, uint32_t cls) {
+  if (log_n <= 12) return split_4096(log_n);
+  if (log_n == 16) return 4;
+  if (cls == 2) return log_n - 11;
+  return log_n == 13 ? 0u : log_n == 14 ? 2u : 4u;
 }
 
 // Bounded waits of the single-launch form: polls before a wait gives up, and
@@ -153,14 +173,18 @@ inline uint32_t col_block_for(const ntt_plan_s* p, uint32_t batch) {
   return tuned_col_block(p->log_n, (uint32_t)dominant_class(p), (uint64_t)batch * p->L, 256u);
 }
 
+// Values per thread of product rows.  Measured (product / forward-and-multiply, us,
+// radix-8 against radix-16): 64-bit integers 3 x 11 limbs of 2^14 31 / 24 against
+// 36 / 28, 2 x 36 of 2^16 139 / 98 against 135 / 100; fp64 with rows up to 2^11 words
+// 4 limbs of 2^14 15 / 10 against 17 / 12, 144 43 / 33 against 44 / 35; fp64 with
+// 2^12-word rows 2 x 36 of 2^16 90 against 86.
 inline int polymul_rb_for(const ntt_plan_s* p, uint32_t split, uint32_t batch) {
   const int n2 = (int)p->log_n - (int)split;
   if (!row_rb_ok(3, n2)) return 4;
   if (p->row_rb == 3 || p->row_rb == 4) return p->row_rb;
-  // measured on 2 x 36 x 2^16: radix-16 rows 46 us, radix-8 52 us (two-pass)
-  const uint32_t fallback = split ? 4u : 3u;
-  const int rb = (int)tuned_row_rb(4u, p->log_n, (uint32_t)dominant_class(p),
-                                   (uint64_t)batch * p->L, fallback);
+  const int cls = dominant_class(p);
+  const uint32_t fallback = (split && cls != 2 && n2 > 11) ? 4u : 3u;
+  const int rb = (int)tuned_row_rb(4u, p->log_n, (uint32_t)cls, (uint64_t)batch * p->L, fallback);
   return rb == 3 ? 3 : 4;
 }
 
@@ -188,10 +212,38 @@ inline bool xprod_fits(const ntt_plan_s* p, uint32_t rows, uint32_t cols, const 
   return (reinterpret_cast<uintptr_t>(key) & 15u) == 0;
 }
 
-// Split used by one call over `batch` polynomials.
+// Split used by one call over `batch` polynomials.  N = 2^14 in the fp64 classes
+// runs in one pass (a workgroup of 139 KB of LDS per compute unit) when there are
+// enough limb-rows to fill the chip with them (forward / inverse, us, against two
+// passes: 144 rows 16 / 18 and 22 / 26, 324 rows 31 / 34 and 35 / 38, 36 rows 14 / 15
+// and 13 / 13).
 inline uint32_t call_split(const ntt_plan_s* p, uint32_t batch) {
   if (p->forced_split >= 0) return (uint32_t)p->forced_split;
-  return tuned_split_for(p->log_n, (uint32_t)dominant_class(p), (uint64_t)batch * p->L, p->log_n1);
+  const uint32_t cls = (uint32_t)dominant_class(p);
+  const uint64_t rows = (uint64_t)batch * p->L;
+  const uint32_t fallback = p->size_split && p->log_n == 14 && cls != 2 && rows >= 96 ? 0u : p->log_n1;
+  return tuned_split_for(p->log_n, cls, rows, fallback);
+}
+
+// Split of polymul (and forward-and-multiply) over `batch` pairs; `table_batch`:
+// the polynomials whose tuned split it takes.  The table's single pass at N = 2^14
+// is not for product rows (2^13 words at most).  Otherwise the fp64 classes run
+// N = 2^13 in one pass from 64 limb-rows on (product / forward-and-multiply, us: 72
+// rows 20 / 18 against 23 / 19, 144 21 / 19 against 35 / 26), below that in rows of
+// 2^10 words (8 rows 15 / 10 against 17 / 13), and 2^14 in rows of 2^10 words (144
+// rows 43 / 33 against 47 / 37).
+inline uint32_t polymul_call_split(const ntt_plan_s* p, uint32_t batch, uint32_t table_batch) {
+  if (p->forced_split >= 0) return polymul_split_log(p->log_n, (uint32_t)p->forced_split);
+  const uint32_t cls = (uint32_t)dominant_class(p);
+  const uint32_t tuned = tuned_split_for(p->log_n, cls, (uint64_t)table_batch * p->L, ~0u);
+  if (tuned != ~0u && !(tuned == 0 && p->log_n == 14)) return polymul_split_log(p->log_n, tuned);
+  if (!p->size_split || cls == 2 || p->log_n < 13 || p->log_n > 14)
+    return polymul_split_log(p->log_n, p->log_n1);
+  if (p->log_n == 13) return (uint64_t)batch * p->L >= 64 ? 0u : 3u;
+  return 4;
+}
+inline uint32_t polymul_call_split(const ntt_plan_s* p, uint32_t batch) {
+  return polymul_call_split(p, batch, batch);
 }
 
 // Polymul with a caller-provided workspace of polymul_ws_bytes(p, batch) bytes

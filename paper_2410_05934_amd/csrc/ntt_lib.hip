@@ -66,12 +66,6 @@ static uint64_t root_of(uint32_t N, uint64_t q) {
 // ---------------------------------------------------------------------------
 // Plan
 
-static uint32_t default_split(int log_n) {
-  if (log_n < 4) return (uint32_t)log_n;   // whole transform in the column kernel
-  if (log_n <= 12) return 0;               // single on-chip pass
-  return (uint32_t)(log_n - 12);           // column pass + 4096-word rows
-}
-
 bool nttk::split_valid(int log_n, int n1) {
   if (n1 == 0) return log_n >= 4 && log_n <= 14;
   if (n1 == log_n) return log_n <= 5;
@@ -397,20 +391,20 @@ static ntt_status transform_entry(ntt_plan_t plan, void* data, uint32_t batch, b
 
 namespace nttk {
 size_t polymul_ws_bytes(const ntt_plan_s* p, uint32_t batch) {
-  const uint32_t split = polymul_split(p, call_split(p, batch));
+  const uint32_t split = polymul_call_split(p, batch);
   return split ? ((size_t)batch * p->L << p->log_n) * (p->word_bits / 8) : 0;
 }
 
 ntt_status polymul_into(const ntt_plan_s* plan, void* out, const void* a, const void* b,
                         uint32_t batch, void* ws, hipStream_t s) {
-  const uint32_t split = polymul_split(plan, call_split(plan, batch));
+  const uint32_t split = polymul_call_split(plan, batch);
   if (split && !ws) return fail(NTT_EINVAL, "polymul workspace missing");
   NTT_FOR_CLASSES(plan, (polymul_cls<A>(plan, c, out, a, b, ws, batch, split, s)));
   return NTT_OK;
 }
 
 bool polymul_rows_ok(const ntt_plan_s* p, uint32_t batch) {
-  const uint32_t split = polymul_split(p, call_split(p, batch));
+  const uint32_t split = polymul_call_split(p, batch);
   return split > 0 && split < p->log_n;
 }
 
@@ -419,7 +413,7 @@ ntt_status polymul_rows_into(const ntt_plan_s* plan, const uint64_t* out_rows, c
                              hipStream_t s) {
   if (!polymul_rows_ok(plan, batch)) return fail(NTT_EINVAL, "polymul through row tables needs two passes");
   if (!o || !ws || !out_rows || !a_rows || !b_rows) return fail(NTT_EINVAL, "null argument");
-  const uint32_t split = polymul_split(plan, call_split(plan, batch));
+  const uint32_t split = polymul_call_split(plan, batch);
   NTT_FOR_CLASSES(plan, (polymul_rows_cls<A>(plan, c, out_rows, a_rows, b_rows, o, ws, batch, split, s)));
   return NTT_OK;
 }
@@ -479,7 +473,7 @@ ntt_status ntt_plan_create(ntt_plan_t* out, uint32_t N, const uint64_t* moduli,
   if ((flags & NTT_FLAG_ROW_RADIX8) && (flags & NTT_FLAG_ROW_RADIX4))
     return fail(NTT_EINVAL, "NTT_FLAG_ROW_RADIX8 and NTT_FLAG_ROW_RADIX4 are exclusive");
   const int log_n = ilog2(N);
-  uint32_t n1 = default_split(log_n);
+  uint32_t n1 = split_4096((uint32_t)log_n);
   if (flags & NTT_FLAG_SPLIT_MASK) {
     const int forced = (int)((flags & NTT_FLAG_SPLIT_MASK) >> 8) - 1;
     if (!split_valid(log_n, forced)) return fail(NTT_EINVAL, "split n1=%d invalid for N=%u", forced, N);
@@ -507,6 +501,9 @@ ntt_status ntt_plan_create(ntt_plan_t* out, uint32_t N, const uint64_t* moduli,
     free_plan(p);
     return st;
   }
+  p->size_split = p->forced_split < 0 &&
+                  !(flags & (NTT_FLAG_FUSED | NTT_FLAG_ROW_RADIX8 | NTT_FLAG_ROW_RADIX4));
+  if (p->size_split) p->log_n1 = default_split(p->log_n, (uint32_t)dominant_class(p));
   *out = p;
   return NTT_OK;
 }
@@ -789,8 +786,8 @@ ntt_status ntt_forward_mul(ntt_plan_t plan, void* out, void* a, void* b, uint32_
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = validate_words(plan, a, batch, s, "a")) != NTT_OK) return st;
   if ((st = validate_words(plan, b, batch, s, "b")) != NTT_OK) return st;
-  // the split of a forward over all 2 * batch polynomials, restricted as polymul's
-  const uint32_t split = polymul_split(plan, call_split(plan, 2 * batch));
+  // a tuned split is that of a forward over all 2 * batch polynomials
+  const uint32_t split = polymul_call_split(plan, batch, 2 * batch);
   NTT_FOR_CLASSES(plan, (fwdmul_cls<A>(plan, c, out, a, b, batch, split, s)));
   return NTT_OK;
 }

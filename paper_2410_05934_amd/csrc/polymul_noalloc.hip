@@ -67,10 +67,17 @@ ntt_status ntt_polymul_noalloc(ntt_plan_t plan, void* out, const void* a, const 
   if (plan->flags & NTT_FLAG_VALIDATE)
     return fail(NTT_EINVAL, "plans with NTT_FLAG_VALIDATE allocate and wait for the range check; "
                             "use ntt_polymul");
+  // Lengths above 2^12 are bound to the array's size even where a call's split needs
+  // no workspace, unless the plan or the tuning table fixes a single pass.
+  const uint32_t rows12 = plan->forced_split >= 0 ? (uint32_t)plan->forced_split
+                          : tuned_split_for(plan->log_n, (uint32_t)dominant_class(plan),
+                                            (uint64_t)batch * plan->L, split_4096(plan->log_n));
   const size_t bytes = polymul_ws_bytes(plan, batch);
-  if (bytes > kScratchBytes)
+  const size_t bound = polymul_split_log(plan->log_n, rows12)
+                           ? ((size_t)batch * plan->L << plan->log_n) * (plan->word_bits / 8) : 0;
+  if (bytes > kScratchBytes || bound > kScratchBytes)
     return fail(NTT_EINVAL, "workspace of %zu bytes exceeds the %zu-byte scratch (batch * L * N * word "
-                            "bytes for two-pass products)", bytes, kScratchBytes);
+                            "bytes for two-pass products)", bytes > bound ? bytes : bound, kScratchBytes);
   void* ws = nullptr;
   if (bytes) {
     const ntt_status st = scratch_on_current_device(&ws);

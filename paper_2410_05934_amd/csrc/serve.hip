@@ -277,6 +277,7 @@ struct ntt_server_s {
       vp.log_n = plan->log_n;
       vp.word_bits = plan->word_bits;
       vp.log_n1 = plan->log_n1;
+      vp.size_split = plan->size_split;
       for (const Req* q : b->reqs) {
         ntt_plan_t qp = plan_for(q, &st);
         if (!qp) return st;

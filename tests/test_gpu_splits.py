@@ -1,0 +1,55 @@
+"""GPU parity: the split and row radix a call takes by default, on both sides of
+the rules' lines, against a plan with the split fixed (whose words other tests pin
+to the oracle) and, for one row of each, the oracle itself."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2410_05934_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2410_05934_amd as ntt  # noqa: E402
+from paper_2410_05934_amd.tensors import to_host  # noqa: E402
+
+PRIMES = {"u32": (32, 32), "fp64": (50, 64), "i64": (60, 64)}
+
+
+@pytest.mark.parametrize("cls", list(PRIMES))
+@pytest.mark.parametrize("logn,batch", [(13, 1), (13, 21), (13, 22), (13, 70), (14, 1), (14, 31),
+                                        (14, 32), (15, 1), (15, 40), (16, 2)])
+def test_default_split_gives_the_same_words(cls, logn, batch):
+    bits, wb = PRIMES[cls]
+    N, L = 1 << logn, 3
+    mods = synth.primes_below(1 << bits, 1 << 17, L)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(logn * 100 + batch)
+    dt = torch.int32 if wb == 32 else torch.int64
+
+    def draw():
+        return torch.stack([torch.randint(0, q, (batch, N), device="cuda", generator=g).to(dt)
+                            for q in mods], dim=1)
+
+    a, b = draw(), draw()
+    plan = ntt.Plan(N, mods, wb)
+    fixed = ntt.Plan(N, mods, wb, ntt.flag_split(logn - 12))
+    got = {}
+    for name, p in (("default", plan), ("fixed", fixed)):
+        f, i, c, u, v = a.clone(), a.clone(), torch.empty_like(a), a.clone(), b.clone()
+        p.forward(f)
+        p.inverse(i)
+        p.polymul(c, a, b)
+        m = torch.empty_like(a)
+        p.forward_mul(m, u, v)
+        got[name] = (f, i, c, m, u, v)
+    torch.cuda.synchronize()
+    for x, y in zip(got["default"], got["fixed"]):
+        assert torch.equal(x, y)
+    word = lambda t: to_host(t, wb).astype(np.uint64)  # noqa: E731
+    last = word(a[-1:])
+    assert np.array_equal(word(got["default"][0][-1:]), oracle.forward(last, mods))
+    assert np.array_equal(word(got["default"][1][-1:]), oracle.inverse(last, mods))

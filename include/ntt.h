@@ -397,8 +397,8 @@ typedef struct ntt_ragged_s* ntt_ragged_t;
  * item; a product item transforms a and b, multiplies and inverse-transforms
  * in registers/LDS -- built on the host, sorted largest first, uploaded once
  * and run by one persistent launch per word width.  Jobs of N >= 2^13 are
- * grouped by (N, arithmetic class, kind): every limb-row of a group goes into
- * one row table, and one column launch plus one row launch cover a transform
+ * grouped by (arithmetic class, kind): every limb-row of a group, whatever its
+ * N, goes into one row table, and one column launch plus one row launch cover a transform
  * group (a product group: one column launch over both operands, the fused
  * product rows, one inverse column launch), as the batched calls do for one
  * plan.  With NTT_RAGGED_IN_WORKGROUP they go into the persistent kernel too

@@ -291,42 +291,70 @@ __global__ void __launch_bounds__(kRaggedBlock, 4) ragged_kernel(RaggedArgs args
 
 // ---------------------------------------------------------------------------
 // Grouped two-pass launches for the large transforms of a batch (N >= 2^13):
-// every limb-row of one (N, class, direction) goes into one row table, and one
-// column launch plus one row launch (2^12-word rows) cover all of them, as the
-// batched transform does for one plan.  Table rows are sorted by prime, and
-// row chunks are ordered row-fastest, so neighbouring workgroups share twiddles.
+// every limb-row of one (class, direction), whatever its N, goes into one row
+// table, and one column launch plus one row launch (2^12-word rows) cover all of
+// them, as the batched transform does for one plan.  A launch's table is a run of
+// segments, one per N, the longest first; a workgroup finds its segment from its
+// index, so it is one scalar search of at most four.  Rows of a segment are sorted
+// by prime, and row chunks are ordered row-fastest, so neighbouring workgroups share
+// twiddles.  (One pair of launches per N and class left most of a batch to launches
+// of 60 to 700 workgroups, one or two at a time, and the chip mostly idle.  Mixes of
+// 96 / 48 / 24 plans, 0.64 / 0.33 / 0.16 GB: 348 / 252 / 145 -> 326 / 205 / 106 us.)
 struct RowRef {
   void* data;          // 2^log_n words of one limb-row (written)
   const void* src;     // the words read by a column pass that is not in place
   const LimbDev* ld;   // its modulus (device copy inside the owning plan)
 };
 
-struct GangArgs {
-  const RowRef* rows;
+constexpr int kGangLogN2 = 12;
+constexpr uint32_t kGangSegs = 4;  // log2 N = 13 .. 16
+
+struct GangSeg {
+  uint32_t row0;       // first table row
   uint32_t n_rows;
   uint32_t log_n1;     // column stages; rows are 2^12 words
-  uint32_t from_src;   // column pass reads rows[i].src (else rows[i].data, in place)
+  uint32_t first;      // first unit of this segment (column launch: rows; else chunks)
 };
 
-constexpr int kGangLogN2 = 12;
+struct GangArgs {
+  const RowRef* rows;
+  uint32_t n_seg;
+  uint32_t units;      // rows or chunks of all segments
+  uint32_t from_src;   // column pass reads rows[i].src (else rows[i].data, in place)
+  GangSeg seg[kGangSegs];
+};
 
-template <class A, int LOGN1, bool INV>
-__global__ void __launch_bounds__(kColBlock) gang_col_kernel(GangArgs g) {
-  using W = typename A::W;
-  const uint32_t gid = blockIdx.x * kColBlock + threadIdx.x;
-  const bool valid = gid < (g.n_rows << kGangLogN2);
-  const uint32_t x = valid ? gid : 0;
-  // a workgroup's columns lie in one row: its entry is read through scalar registers
-  const RowRef rr = g.rows[__builtin_amdgcn_readfirstlane(x >> kGangLogN2)];
-  const uint32_t r = x & ((1u << kGangLogN2) - 1u);
-  W* p = reinterpret_cast<W*>(rr.data);
-  const W* q = g.from_src ? reinterpret_cast<const W*>(rr.src) : p;
-  col_one<A, LOGN1, INV, true>(p, q, *rr.ld, kGangLogN2, r, valid);
+// The segment of unit k (k < units).
+__device__ __forceinline__ GangSeg gang_seg(const GangArgs& g, uint32_t k) {
+  GangSeg s = g.seg[0];
+#pragma unroll
+  for (uint32_t i = 1; i < kGangSegs; ++i)
+    if (i < g.n_seg && k >= g.seg[i].first) s = g.seg[i];
+  return s;
 }
 
-// Fused product rows of a polymul group: the table holds n_rows product rows
-// (data = out, intermediate of a) followed by n_rows workspace rows (data =
-// intermediate of b); chunk c of product row i reads both intermediates and
+// Column pass: units are limb-rows, 2^12 / kColBlock workgroups each.
+template <class A, bool INV>
+__global__ void __launch_bounds__(kColBlock) gang_col_kernel(GangArgs g) {
+  using W = typename A::W;
+  constexpr uint32_t kPer = (1u << kGangLogN2) / kColBlock;
+  const uint32_t k = blockIdx.x / kPer;
+  const GangSeg sg = gang_seg(g, k);
+  const RowRef rr = g.rows[sg.row0 + (k - sg.first)];
+  const uint32_t r = (blockIdx.x % kPer) * kColBlock + threadIdx.x;
+  W* p = reinterpret_cast<W*>(rr.data);
+  const W* q = g.from_src ? reinterpret_cast<const W*>(rr.src) : p;
+  switch (sg.log_n1) {
+    case 1: col_one<A, 1, INV, true>(p, q, *rr.ld, kGangLogN2, r, true); break;
+    case 2: col_one<A, 2, INV, true>(p, q, *rr.ld, kGangLogN2, r, true); break;
+    case 3: col_one<A, 3, INV, true>(p, q, *rr.ld, kGangLogN2, r, true); break;
+    default: col_one<A, 4, INV, true>(p, q, *rr.ld, kGangLogN2, r, true); break;
+  }
+}
+
+// Fused product rows of the polymul groups: a segment's table rows are n_rows
+// product rows (data = out, intermediate of a) followed by n_rows workspace rows
+// (data = intermediate of b); chunk c of product row i reads both intermediates and
 // writes the product's intermediate over out.
 template <class A>
 __global__ void __launch_bounds__((RowShape<kGangLogN2, 4>::BLOCK), 4) gang_pm_row_kernel(GangArgs g) {
@@ -335,16 +363,14 @@ __global__ void __launch_bounds__((RowShape<kGangLogN2, 4>::BLOCK), 4) gang_pm_r
   using V = typename A::V;
   using W = typename A::W;
   __shared__ V lds[S::LDS_ELEMS];
-  const uint32_t total = g.n_rows << g.log_n1;
-  const uint32_t k0 = xcd_block(blockIdx.x, gridDim.x);
-  const bool valid = k0 < total;
-  const uint32_t k = valid ? k0 : 0;
-  const uint32_t i = k % g.n_rows, c = k / g.n_rows;
-  const RowRef ra = g.rows[i], rb = g.rows[i + g.n_rows];
+  const uint32_t k = xcd_block(blockIdx.x, gridDim.x);  // grid: one workgroup per chunk
+  const GangSeg sg = gang_seg(g, k);
+  const uint32_t i = (k - sg.first) % sg.n_rows, c = (k - sg.first) / sg.n_rows;
+  const RowRef ra = g.rows[sg.row0 + i], rb = g.rows[sg.row0 + sg.n_rows + i];
   W* p = reinterpret_cast<W*>(ra.data) + ((uint64_t)c << kGangLogN2);
   const W* q = reinterpret_cast<const W*>(rb.data) + ((uint64_t)c << kGangLogN2);
-  polymul_chunk<A, kGangLogN2, true, 4>(p, p, q, *ra.ld, (1u << g.log_n1) + c, threadIdx.x, lds,
-                                        valid);
+  polymul_chunk<A, kGangLogN2, true, 4>(p, p, q, *ra.ld, (1u << sg.log_n1) + c, threadIdx.x, lds,
+                                        true);
 }
 
 template <class A, bool INV>
@@ -354,63 +380,80 @@ __global__ void __launch_bounds__((RowShape<kGangLogN2, 4>::BLOCK), 4) gang_row_
   using V = typename A::V;
   using W = typename A::W;
   __shared__ V lds[S::LDS_ELEMS];
-  const uint32_t total = g.n_rows << g.log_n1;
-  const uint32_t k0 = xcd_block(blockIdx.x, gridDim.x);
-  const bool valid = k0 < total;
-  const uint32_t k = valid ? k0 : 0;
-  const uint32_t i = k % g.n_rows, c = k / g.n_rows;
-  const RowRef rr = g.rows[i];
+  const uint32_t k = xcd_block(blockIdx.x, gridDim.x);  // grid: one workgroup per chunk
+  const GangSeg sg = gang_seg(g, k);
+  const uint32_t i = (k - sg.first) % sg.n_rows, c = (k - sg.first) / sg.n_rows;
+  const RowRef rr = g.rows[sg.row0 + i];
   W* p = reinterpret_cast<W*>(rr.data) + ((uint64_t)c << kGangLogN2);
-  row_chunk<A, kGangLogN2, INV, true, 4>(p, p, *rr.ld, (1u << g.log_n1) + c, threadIdx.x, lds,
-                                         valid);
+  row_chunk<A, kGangLogN2, INV, true, 4>(p, p, *rr.ld, (1u << sg.log_n1) + c, threadIdx.x, lds, true);
+}
+
+// The launches of one group.  `seg` holds the segments' rows (row0, n_rows, log_n1);
+// the unit counts are filled in here: `chunks` for row launches, else rows, `mult`
+// table rows per segment row (2: product and workspace rows).
+inline GangArgs gang_args(const RowRef* rows, const GangSeg* seg, uint32_t n_seg, bool chunks,
+                          uint32_t mult = 1) {
+  GangArgs g;
+  g.rows = rows;
+  g.n_seg = n_seg;
+  g.from_src = 0;
+  g.units = 0;
+  for (uint32_t i = 0; i < kGangSegs; ++i) {
+    g.seg[i] = seg[i < n_seg ? i : 0];
+    if (i >= n_seg) continue;
+    g.seg[i].first = g.units;
+    g.seg[i].n_rows *= mult;
+    g.units += chunks ? g.seg[i].n_rows << g.seg[i].log_n1 : g.seg[i].n_rows;
+  }
+  return g;
+}
+
+inline uint64_t gang_words(const GangSeg* seg, uint32_t n_seg) {
+  uint64_t w = 0;
+  for (uint32_t i = 0; i < n_seg; ++i) w += (uint64_t)seg[i].n_rows << (seg[i].log_n1 + kGangLogN2);
+  return w;
 }
 
 template <class A, bool INV>
-hipError_t launch_gang_col(const GangArgs& g, hipStream_t s, bool timed) {
-  const uint32_t cols = g.n_rows << kGangLogN2;
-  const uint64_t words = (uint64_t)g.n_rows << (g.log_n1 + kGangLogN2);
-  LaunchTimer t(timed ? "gang_col" : nullptr, A::kName, (int)g.log_n1, INV, true, words, s);
-  const dim3 grid((cols + kColBlock - 1) / kColBlock);
-  switch (g.log_n1) {
-    case 1: hipLaunchKernelGGL((gang_col_kernel<A, 1, INV>), grid, dim3(kColBlock), 0, s, g); break;
-    case 2: hipLaunchKernelGGL((gang_col_kernel<A, 2, INV>), grid, dim3(kColBlock), 0, s, g); break;
-    case 3: hipLaunchKernelGGL((gang_col_kernel<A, 3, INV>), grid, dim3(kColBlock), 0, s, g); break;
-    case 4: hipLaunchKernelGGL((gang_col_kernel<A, 4, INV>), grid, dim3(kColBlock), 0, s, g); break;
-    default: return hipErrorInvalidValue;
-  }
+hipError_t launch_gang_col(const GangArgs& g, uint64_t words, hipStream_t s, bool timed) {
+  LaunchTimer t(timed ? "gang_col" : nullptr, A::kName, (int)g.seg[0].log_n1, INV, true, words, s);
+  hipLaunchKernelGGL((gang_col_kernel<A, INV>), dim3(g.units * ((1u << kGangLogN2) / kColBlock)),
+                     dim3(kColBlock), 0, s, g);
   return hipGetLastError();
 }
 
-// A polymul group (table: n product rows, then n workspace rows): forward column
-// passes of a and b over all 2n rows in one launch, the fused product rows, the
-// inverse column pass of the product rows.
+// Products: forward column passes of a and b over all product and workspace rows in
+// one launch, the fused product rows, the inverse column pass of the product rows.
 template <class A>
-hipError_t launch_gang_pm(GangArgs g, hipStream_t s, bool timed) {
-  GangArgs both = g;
-  both.n_rows = 2 * g.n_rows;
+hipError_t launch_gang_pm(const RowRef* rows, const GangSeg* seg, uint32_t n_seg, hipStream_t s,
+                          bool timed) {
+  const uint64_t words = gang_words(seg, n_seg);
+  GangArgs both = gang_args(rows, seg, n_seg, false, 2);
   both.from_src = 1;
-  hipError_t e = launch_gang_col<A, false>(both, s, timed);
+  hipError_t e = launch_gang_col<A, false>(both, 2 * words, s, timed);
   if (e != hipSuccess) return e;
   {
-    const uint64_t words = (uint64_t)g.n_rows << (g.log_n1 + kGangLogN2);
+    const GangArgs g = gang_args(rows, seg, n_seg, true);
     LaunchTimer t(timed ? "gang_polymul_row" : nullptr, A::kName, kGangLogN2, false, true, words, s);
-    hipLaunchKernelGGL((gang_pm_row_kernel<A>), dim3(g.n_rows << g.log_n1),
-                       dim3(RowShape<kGangLogN2, 4>::BLOCK), 0, s, g);
+    hipLaunchKernelGGL((gang_pm_row_kernel<A>), dim3(g.units), dim3(RowShape<kGangLogN2, 4>::BLOCK),
+                       0, s, g);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  g.from_src = 0;
-  return launch_gang_col<A, true>(g, s, timed);
+  return launch_gang_col<A, true>(gang_args(rows, seg, n_seg, false), words, s, timed);
 }
 
 template <class A, bool INV>
-hipError_t launch_gang(const GangArgs& g, hipStream_t s, bool timed) {
-  const uint32_t chunks = g.n_rows << g.log_n1;
-  const uint64_t words = (uint64_t)g.n_rows << (g.log_n1 + kGangLogN2);
-  auto col = [&]() -> hipError_t { return launch_gang_col<A, INV>(g, s, timed); };
+hipError_t launch_gang(const RowRef* rows, const GangSeg* seg, uint32_t n_seg, hipStream_t s,
+                       bool timed) {
+  const uint64_t words = gang_words(seg, n_seg);
+  auto col = [&]() -> hipError_t {
+    return launch_gang_col<A, INV>(gang_args(rows, seg, n_seg, false), words, s, timed);
+  };
   auto row = [&]() -> hipError_t {
+    const GangArgs g = gang_args(rows, seg, n_seg, true);
     LaunchTimer t(timed ? "gang_row" : nullptr, A::kName, kGangLogN2, INV, true, words, s);
-    hipLaunchKernelGGL((gang_row_kernel<A, INV>), dim3(chunks),
-                       dim3(RowShape<kGangLogN2, 4>::BLOCK), 0, s, g);
+    hipLaunchKernelGGL((gang_row_kernel<A, INV>), dim3(g.units), dim3(RowShape<kGangLogN2, 4>::BLOCK),
+                       0, s, g);
     return hipGetLastError();
   };
   hipError_t e = INV ? row() : col();
@@ -438,7 +481,9 @@ struct ntt_ragged_s {
   uint32_t grid[2] = {0, 0};
   // grouped launches of the N >= 2^13 transforms
   struct Gang {
-    uint32_t cls, log_n, op, off, n;  // polymul: table rows off .. off + 2n - 1
+    uint32_t cls, op, n_seg;
+    uint32_t n;              // limb-rows (products count once)
+    GangSeg seg[kGangSegs];  // polymul: n_rows product rows, then as many workspace rows
   };
   std::vector<Gang> gangs;
   RowRef* d_rows = nullptr;
@@ -507,21 +552,15 @@ hipError_t launch_all(ntt_ragged_s* r, hipStream_t s, bool timed,
   for (size_t i = 0; i < r->gangs.size(); ++i) {
     const auto& gg = r->gangs[i];
     hipStream_t gs = fork ? (*branches)[i % branches->size()] : s;
-    GangArgs g;
-    g.rows = r->d_rows + gg.off;
-    g.n_rows = gg.n;
-    g.log_n1 = gg.log_n - kGangLogN2;
-    g.from_src = 0;
-    if (gg.op == kOpMul) {
-      if (gg.cls == 0) e = launch_gang_pm<ArF64S>(g, gs, timed);
-      else if (gg.cls == 1) e = launch_gang_pm<ArF64L>(g, gs, timed);
-      else e = launch_gang_pm<ArI64>(g, gs, timed);
-    } else {
-      const bool inv = gg.op == kOpInv;
-      if (gg.cls == 0) e = inv ? launch_gang<ArF64S, true>(g, gs, timed) : launch_gang<ArF64S, false>(g, gs, timed);
-      else if (gg.cls == 1) e = inv ? launch_gang<ArF64L, true>(g, gs, timed) : launch_gang<ArF64L, false>(g, gs, timed);
-      else e = inv ? launch_gang<ArI64, true>(g, gs, timed) : launch_gang<ArI64, false>(g, gs, timed);
-    }
+    const RowRef* rows = r->d_rows;
+    auto go = [&](auto ar) -> hipError_t {
+      using A = decltype(ar);
+      if (gg.op == kOpMul) return launch_gang_pm<A>(rows, gg.seg, gg.n_seg, gs, timed);
+      if (gg.op == kOpInv) return launch_gang<A, true>(rows, gg.seg, gg.n_seg, gs, timed);
+      return launch_gang<A, false>(rows, gg.seg, gg.n_seg, gs, timed);
+    };
+    const LimbDev none{};
+    e = gg.cls == 0 ? go(ArF64S(none)) : gg.cls == 1 ? go(ArF64L(none)) : go(ArI64(none));
     if (e != hipSuccess) {
       cleanup();
       return e;
@@ -697,22 +736,37 @@ ntt_status ntt_ragged_create(ntt_ragged_t* out, const ntt_job* jobs, uint32_t n,
     }
     std::stable_sort(v.begin(), v.end(),
                      [](const GroupRow& x, const GroupRow& y) { return x.tw < y.tw; });
-    ntt_ragged_s::Gang gg;
-    gg.cls = std::get<0>(kv.first);
-    gg.log_n = std::get<1>(kv.first);
-    gg.op = op;
-    gg.off = (uint32_t)table.size();
-    gg.n = (uint32_t)v.size();
-    for (const auto& x : v) table.push_back(x.r);
-    if (op == kOpMul) {
-      for (const auto& x : v) {
-        RowRef w = x.r2;
-        w.data = static_cast<unsigned char*>(r->d_ws) + reinterpret_cast<uintptr_t>(x.r2.data);
-        table.push_back(w);
-      }
-    }
-    r->gangs.push_back(gg);
   }
+  // One group per (class, operation); its segments from the longest N down.
+  for (uint32_t cls = 0; cls < 3; ++cls)
+    for (uint32_t op : {kOpFwd, kOpInv, kOpMul}) {
+      ntt_ragged_s::Gang gg{};
+      gg.cls = cls;
+      gg.op = op;
+      for (uint32_t log_n = 16; log_n > 12; --log_n) {
+        const auto it = groups.find(std::make_tuple(cls, log_n, op));
+        if (it == groups.end()) continue;
+        GangSeg& sg = gg.seg[gg.n_seg++];
+        sg.row0 = (uint32_t)table.size();
+        sg.n_rows = (uint32_t)it->second.size();
+        sg.log_n1 = log_n - kGangLogN2;
+        gg.n += sg.n_rows;
+        for (const auto& x : it->second) table.push_back(x.r);
+        if (op != kOpMul) continue;
+        for (const auto& x : it->second) {
+          RowRef w = x.r2;
+          w.data = static_cast<unsigned char*>(r->d_ws) + reinterpret_cast<uintptr_t>(x.r2.data);
+          table.push_back(w);
+        }
+      }
+      if (gg.n_seg) r->gangs.push_back(gg);
+    }
+  // The longest first: they fork first, and the short ones fill in beside them.
+  std::stable_sort(r->gangs.begin(), r->gangs.end(),
+                   [](const ntt_ragged_s::Gang& x, const ntt_ragged_s::Gang& y) {
+                     return gang_words(x.seg, x.n_seg) * (x.op == kOpMul ? 3 : 1) >
+                            gang_words(y.seg, y.n_seg) * (y.op == kOpMul ? 3 : 1);
+                   });
   r->n_items[0] = (uint32_t)narrow.size();
   r->n_items[1] = (uint32_t)wide.size();
   r->items = narrow;

@@ -408,7 +408,7 @@ typedef struct ntt_ragged_s* ntt_ragged_t;
  * jobs must stay valid for the life of the handle. */
 ntt_status ntt_ragged_create(ntt_ragged_t* out, const ntt_job* jobs, uint32_t n, uint32_t flags);
 
-/* Run the batch on `stream`: reset the work counter and launch the persistent
+/* Run the batch on `stream`: launch the persistent
  * kernel(s) and the grouped launches.  Unless NTT_RAGGED_NO_GRAPH was given, the
  * first run captures these launches into a hipGraph and every run replays it.
  * Runs of one handle must not overlap in time (they share the work counter). */

@@ -262,8 +262,9 @@ struct RaggedArgs {
   const RaggedJobDev* jobs;
   const RaggedItem* items;
   uint32_t n_items;
-  uint32_t* counter;
+  uint32_t* counter;  // [0] next item, [kRaggedDone] workgroups that have left
 };
+constexpr uint32_t kRaggedDone = 2;  // two launches' item counters come first
 
 // WIDE = false: 32-bit words (class 0); WIDE = true: 64-bit words (classes 1, 2).
 // Four waves per SIMD (at most 128 VGPRs): each tile shape alone fits, and the
@@ -277,7 +278,16 @@ __global__ void __launch_bounds__(kRaggedBlock, 4) ragged_kernel(RaggedArgs args
     __syncthreads();
     const uint32_t idx = s_item;
     __syncthreads();
-    if (idx >= args.n_items) break;
+    if (idx >= args.n_items) {
+      // The last workgroup to leave clears both counters for the next run: by then
+      // every workgroup has had its last item.  (A launch that cleared them first
+      // held up the start of the captured graph.)
+      if (threadIdx.x == 0 && atomicAdd(args.counter + kRaggedDone, 1u) == gridDim.x - 1u) {
+        atomicExch(args.counter, 0u);
+        atomicExch(args.counter + kRaggedDone, 0u);
+      }
+      break;
+    }
     const RaggedItem& it = args.items[idx];
     const RaggedJobDev& j = args.jobs[it.job];
     if constexpr (WIDE) {
@@ -461,11 +471,6 @@ hipError_t launch_gang(const RowRef* rows, const GangSeg* seg, uint32_t n_seg, h
   return e;
 }
 
-__global__ void zero_counters(uint32_t* c, uint32_t n) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) c[i] = 0;
-}
-
 }  // namespace nttk
 
 using namespace nttk;
@@ -477,7 +482,7 @@ struct ntt_ragged_s {
   uint32_t n_items[2] = {0, 0};  // [narrow, wide]
   RaggedJobDev* d_jobs = nullptr;
   RaggedItem* d_items = nullptr;
-  uint32_t* d_counter = nullptr;  // [2]
+  uint32_t* d_counter = nullptr;  // [4], zero between runs (RaggedArgs::counter)
   uint32_t grid[2] = {0, 0};
   // grouped launches of the N >= 2^13 transforms
   struct Gang {
@@ -526,12 +531,6 @@ hipError_t launch_all(ntt_ragged_s* r, hipStream_t s, bool timed,
       cleanup();
       return e;
     }
-  }
-  hipLaunchKernelGGL(zero_counters, dim3(1), dim3(64), 0, s, r->d_counter, 2u);
-  e = hipGetLastError();
-  if (e != hipSuccess) {
-    cleanup();
-    return e;
   }
   for (int w = 0; w < 2; ++w) {
     if (r->n_items[w] == 0) continue;
@@ -785,7 +784,8 @@ ntt_status ntt_ragged_create(ntt_ragged_t* out, const ntt_job* jobs, uint32_t n,
     r->grid[w] = std::max(1u, std::min<uint32_t>(r->n_items[w], (uint32_t)(cus * std::max(1, per_cu[w]))));
   e = hipMalloc(&r->d_jobs, sizeof(RaggedJobDev) * r->jobs.size());
   if (e == hipSuccess) e = hipMalloc(&r->d_items, sizeof(RaggedItem) * std::max<size_t>(1, r->items.size()));
-  if (e == hipSuccess) e = hipMalloc(&r->d_counter, sizeof(uint32_t) * 2);
+  if (e == hipSuccess) e = hipMalloc(&r->d_counter, sizeof(uint32_t) * 4);
+  if (e == hipSuccess) e = hipMemset(r->d_counter, 0, sizeof(uint32_t) * 4);
   if (e == hipSuccess)
     e = hipMemcpy(r->d_jobs, r->jobs.data(), sizeof(RaggedJobDev) * r->jobs.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess && !r->items.empty())
@@ -812,7 +812,7 @@ ntt_status ntt_ragged_run(ntt_ragged_t r, void* stream) {
     return e == hipSuccess ? NTT_OK : hip_fail(e, "ragged launch");
   }
   if (!r->exec) {
-    // Capture the counter reset and the persistent launch(es) once.
+    // Capture the persistent launch(es) and the groups once.
     hipStream_t cap = nullptr;
     hipError_t e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
     if (e != hipSuccess) return hip_fail(e, "hipStreamCreate");

@@ -127,8 +127,8 @@ bool split_valid(int log_n, int n1);
 // Values per thread (log2) of row passes: forced by NTT_FLAG_ROW_RADIX8 or
 // NTT_FLAG_ROW_RADIX4, else the tuning table, else radix-4 for forward and
 // inverse rows of calls in the 64-bit integer class with at most kLatencyChunks
-// row chunks, radix-8 for inverse rows, forward rows of 2^10..2^11 words and
-// single-pass polymul rows, and radix-16 for the rest.
+// row chunks, radix-8 for inverse rows and forward rows of 2^10..2^11 words, and
+// radix-16 for the rest (product rows: polymul_rb_for).
 uint32_t tuned_row_rb(uint32_t kind, uint32_t log_n, uint32_t cls, uint64_t rows, uint32_t fallback);
 inline int dominant_class(const ntt_plan_s* p) {
   uint32_t best = 0, cnt = 0;

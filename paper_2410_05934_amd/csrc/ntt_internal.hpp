@@ -202,13 +202,17 @@ inline bool fused_for(const ntt_plan_s* p, bool inv, uint32_t split, uint32_t ba
 }
 
 // Fused external product (one launch per class): N = 2^4 .. 2^12, cols <= rows,
-// at most 1024 threads (rows * N/16) and 64 KiB of LDS (rows * (N + N/16)
-// values) per workgroup, key 16-byte aligned.
+// at most 1024 threads (rows * N/16) and 160 KiB of LDS (rows * (N + N/16)
+// values: all a compute unit has) per workgroup, key 16-byte aligned.  Past 64 KiB a
+// workgroup soon has a compute unit to itself, which is still far from the seven
+// launches and two workspaces of the separate steps (CMux at 2^11, u32: 342
+// ciphertexts of 6 rows 87 -> 33 us, 18 of 8 rows 82 -> 20 us).
+constexpr uint64_t kXprodLds = 160 * 1024;
 inline bool xprod_fits(const ntt_plan_s* p, uint32_t rows, uint32_t cols, const void* key) {
   if (p->log_n < 4 || p->log_n > 12 || cols > rows) return false;
   const uint64_t n = 1ull << p->log_n;
   if ((uint64_t)rows * (n / 16) > 1024) return false;
-  if ((uint64_t)rows * (n + n / 16) * 8 > 65536) return false;
+  if ((uint64_t)rows * (n + n / 16) * 8 > kXprodLds) return false;
   return (reinterpret_cast<uintptr_t>(key) & 15u) == 0;
 }
 

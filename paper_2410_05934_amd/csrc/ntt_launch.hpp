@@ -473,24 +473,25 @@ hipError_t launch_xprod_n(const XpArgs& x, uint32_t groups, hipStream_t s) {
   LaunchTimer t(x.rot ? "cmux" : x.levels ? "xprod_dec" : "xprod", A::kName, LOGN2, false, false,
                 ((uint64_t)groups * x.cols * x.n_cls) << LOGN2, s);
   const dim3 grid(groups * x.n_cls), block(threads);
+  auto go = [&](auto kernel) -> hipError_t {
+    if (lds > 65536) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, grid, block, lds, s, x);
+    return hipGetLastError();
+  };
   if constexpr (LOGN2 >= 10) {
     if (r8) {
-      if (x.rot)
-        hipLaunchKernelGGL((xprod_kernel<A, LOGN2, kXpCmux, 3>), grid, block, lds, s, x);
-      else if (x.levels)
-        hipLaunchKernelGGL((xprod_kernel<A, LOGN2, kXpDecompose, 3>), grid, block, lds, s, x);
-      else
-        hipLaunchKernelGGL((xprod_kernel<A, LOGN2, kXpOperands, 3>), grid, block, lds, s, x);
-      return hipGetLastError();
+      if (x.rot) return go(xprod_kernel<A, LOGN2, kXpCmux, 3>);
+      if (x.levels) return go(xprod_kernel<A, LOGN2, kXpDecompose, 3>);
+      return go(xprod_kernel<A, LOGN2, kXpOperands, 3>);
     }
   }
-  if (x.rot)
-    hipLaunchKernelGGL((xprod_kernel<A, LOGN2, kXpCmux>), grid, block, lds, s, x);
-  else if (x.levels)
-    hipLaunchKernelGGL((xprod_kernel<A, LOGN2, kXpDecompose>), grid, block, lds, s, x);
-  else
-    hipLaunchKernelGGL((xprod_kernel<A, LOGN2, kXpOperands>), grid, block, lds, s, x);
-  return hipGetLastError();
+  if (x.rot) return go(xprod_kernel<A, LOGN2, kXpCmux>);
+  if (x.levels) return go(xprod_kernel<A, LOGN2, kXpDecompose>);
+  return go(xprod_kernel<A, LOGN2, kXpOperands>);
 }
 
 // comps / levels / log_base: the operands are the digits of ciphertexts in `a`

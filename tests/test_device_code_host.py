@@ -1,0 +1,47 @@
+"""Host checks of the compiled kernels: the gfx950 code of the built library,
+disassembled.
+
+  * The kernels of the external product load, rotate and decompose their operands
+    without divergent branches: a branch per element puts each load's latency after
+    the one before (a CMux step of 1000 ciphertexts of 2^8, 50-bit: 9.6 us so, 11.8 with branches).
+"""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2410_05934_amd as ntt
+
+LLVM = "/opt/rocm/llvm/bin"
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """[(symbol, [instruction, ...]), ...] of every device function of the library."""
+    tool = os.path.join(LLVM, "llvm-objdump")
+    if not os.path.exists(tool) or not os.path.exists(ntt.library_path()):
+        pytest.skip("needs the built library and llvm-objdump")
+    d = tmp_path_factory.mktemp("code")
+    lib = shutil.copy(ntt.library_path(), d / "libntt.so")
+    subprocess.run([tool, "--offloading", lib], check=True, capture_output=True, cwd=d)
+    objs = [p for p in sorted(os.listdir(d)) if "gfx950" in p]
+    out = []
+    for p in objs:
+        text = subprocess.run([tool, "-d", "--no-show-raw-insn", "--no-leading-addr", p], check=True,
+                              capture_output=True, text=True, cwd=d).stdout
+        for part in re.split(r"^(?=<\S+>:$)", text, flags=re.M)[1:]:
+            head, *body = part.splitlines()
+            out.append((head.strip("<>:"), [ln.split("//")[0].strip() for ln in body]))
+    assert len(out) > 500
+    return out
+
+
+def test_external_product_operands_load_without_branches(kernels):
+    found = [(n, sum(ln.startswith(("s_and_saveexec", "s_andn2_saveexec")) for ln in body))
+             for n, body in kernels if "xprod_kernel" in n]
+    assert len(found) >= 81  # 9 lengths, 3 operand kinds, 3 classes
+    # a few per kernel (the store of the slots that hold a column), none per element
+    # of a thread's 8 or 16
+    assert [f for f in found if f[1] >= 8] == []

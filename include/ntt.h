@@ -265,9 +265,11 @@ ntt_status ntt_automorph(ntt_plan_t plan, void* out, const void* in, uint32_t ba
  * modified), key [rows][cols][L][N] in the transform domain (the order
  * ntt_forward produces), out [groups][cols][L][N] in natural order; out must
  * not alias a or key.  The same words as ntt_forward on a copy of a, ntt_mac
- * and ntt_inverse on out.  For N <= 2^12 with cols <= rows (and a workgroup of
- * rows * N/16 <= 1024 threads) one launch does everything per group and limb;
- * other shapes take the three steps through a stream-ordered workspace. */
+ * and ntt_inverse on out.  For N <= 2^12 with cols <= rows (a workgroup of
+ * rows * N/16 <= 1024 threads, and up to 64 KiB of its LDS, rows * (N + N/16) * 8
+ * bytes, or 160 KiB where that is the faster form: N >= 2^10, up to 8 rows over
+ * 64-bit integer moduli) one launch does everything per group and limb; other shapes
+ * take the three steps through a stream-ordered workspace. */
 ntt_status ntt_external_product(ntt_plan_t plan, void* out, const void* a, const void* key,
                                 uint32_t rows, uint32_t cols, uint32_t num_operands,
                                 void* stream);
@@ -288,9 +290,9 @@ ntt_status ntt_external_product(ntt_plan_t plan, void* out, const void* a, const
  * [0, B/2]), levels * log_base <= 64 and 1 <= log_base <= 32; the operands, out
  * and key must each hold
  * fewer than 2^32 words (else NTT_EINVAL).  The same words as decomposing into
- * a buffer and calling ntt_external_product on it.  For N <= 2^12 with
- * cols <= comps * levels one launch per class decomposes while it loads;
- * other shapes decompose into a stream-ordered workspace first. */
+ * a buffer and calling ntt_external_product on it.  One launch per class decomposes
+ * while it loads for about the shapes ntt_external_product runs in one; others
+ * decompose into a stream-ordered workspace first. */
 ntt_status ntt_external_product_decomposed(ntt_plan_t plan, void* out, const void* ct,
                                            const void* key, uint32_t num_ct, uint32_t comps,
                                            uint32_t levels, uint32_t log_base, uint32_t cols,
@@ -307,8 +309,8 @@ ntt_status ntt_external_product_decomposed(ntt_plan_t plan, void* out, const voi
  *   rot   device array of num_ct rotation amounts
  *   key   [comps * levels][comps][L][N], transform domain (the RGSW key)
  *   out   [num_ct][comps][L][N]; must not alias acc or key
- * Digit and size rules as ntt_external_product_decomposed.  For N <= 2^12 one
- * launch per class rotates, decomposes, transforms, multiplies-and-accumulates,
+ * Digit and size rules as ntt_external_product_decomposed.  One launch per class
+ * (about the shapes ntt_external_product runs in one) rotates, decomposes, transforms, multiplies-and-accumulates,
  * inverse-transforms and adds; other shapes go through a stream-ordered
  * workspace. */
 ntt_status ntt_cmux(ntt_plan_t plan, void* out, const void* acc, const uint32_t* rot,

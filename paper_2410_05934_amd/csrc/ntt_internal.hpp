@@ -203,17 +203,39 @@ inline bool fused_for(const ntt_plan_s* p, bool inv, uint32_t split, uint32_t ba
 
 // Fused external product (one launch per class): N = 2^4 .. 2^12, cols <= rows,
 // at most 1024 threads (rows * N/16) and 160 KiB of LDS (rows * (N + N/16)
-// values: all a compute unit has) per workgroup, key 16-byte aligned.  Past 64 KiB a
-// workgroup soon has a compute unit to itself, which is still far from the seven
-// launches and two workspaces of the separate steps (CMux at 2^11, u32: 342
-// ciphertexts of 6 rows 87 -> 33 us, 18 of 8 rows 82 -> 20 us).
+// values: all a compute unit has) per workgroup, key 16-byte aligned.
+//   Past 64 KiB a workgroup soon has a compute unit to itself, and one launch is
+// taken only where it beats the separate steps (five launches and a workspace; seven
+// and two with decomposition; XpKind).  Measured, us, separate steps / one launch:
+//   N >= 2^10, fp64 classes: always (u32 CMux at 2^11, 342 ciphertexts of 6 rows
+//     76 / 31; 50-bit products of 16 rows at 2^10, 342 groups 56 / 47).
+//   N >= 2^10, 64-bit integers, whose radix-16 slots spill: operands up to 8 rows
+//     (2^10, 342 groups of 8 rows 54 / 43, of 12 rows 65 / 107), digits up to 12 rows
+//     (342 ciphertexts of 12 rows 112 / 107, of 16 rows 110 / 133), a CMux always
+//     (1000 ciphertexts of 16 rows 295 / 285).
+//   N <= 2^9: every slot of a wave walks all rows, so the work grows with rows^2
+//     (342 groups of 256 rows of 2^6, 50 bits: 83 / 1774; of 1024 rows of 2^4, 60
+//     bits: 472 / 12584).  Only 16 rows of 2^9: over 32-bit words (CMux of 342
+//     ciphertexts 79 / 34, digits 54 / 30; operands up to 512 workgroups, 342 groups
+//     36 / 29, 2048 88 / 113), and a CMux over 50 bits up to 512 workgroups (342: 74 /
+//     71, 1000: 128 / 138).
 constexpr uint64_t kXprodLds = 160 * 1024;
-inline bool xprod_fits(const ntt_plan_s* p, uint32_t rows, uint32_t cols, const void* key) {
+enum XpKind : int { kXpKindOperands = 0, kXpKindDigits = 1, kXpKindCmux = 2 };
+inline bool xprod_fits(const ntt_plan_s* p, XpKind kind, uint32_t rows, uint32_t cols,
+                       uint64_t groups, const void* key) {
   if (p->log_n < 4 || p->log_n > 12 || cols > rows) return false;
   const uint64_t n = 1ull << p->log_n;
   if ((uint64_t)rows * (n / 16) > 1024) return false;
-  if ((uint64_t)rows * (n + n / 16) * 8 > kXprodLds) return false;
-  return (reinterpret_cast<uintptr_t>(key) & 15u) == 0;
+  if ((reinterpret_cast<uintptr_t>(key) & 15u) != 0) return false;
+  const uint64_t lds = (uint64_t)rows * (n + n / 16) * 8;
+  if (lds <= 65536) return true;
+  if (lds > kXprodLds) return false;
+  const int cls = dominant_class(p);
+  if (p->log_n >= 10)
+    return cls != 2 || kind == kXpKindCmux || rows <= (kind == kXpKindDigits ? 12u : 8u);
+  const bool small = groups * p->L <= 512;
+  return p->log_n == 9 && rows <= 16 &&
+         (cls == 0 ? kind != kXpKindOperands || small : cls == 1 && kind == kXpKindCmux && small);
 }
 
 // Split used by one call over `batch` polynomials.  N = 2^14 in the fp64 classes

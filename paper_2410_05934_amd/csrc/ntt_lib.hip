@@ -624,7 +624,7 @@ ntt_status ntt_external_product(ntt_plan_t plan, void* out, const void* a, const
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = validate_words(plan, a, num_operands, s, "a")) != NTT_OK) return st;
   if ((st = validate_words(plan, key, (uint64_t)rows * cols, s, "key")) != NTT_OK) return st;
-  if (xprod_fits(plan, rows, cols, key)) {
+  if (xprod_fits(plan, kXpKindOperands, rows, cols, groups, key)) {
     NTT_FOR_CLASSES(plan, (xprod_cls<A>(plan, c, out, a, key, rows, cols, num_operands, s, 0u, 0u, 0u,
                                         nullptr)));
     return NTT_OK;
@@ -673,7 +673,7 @@ ntt_status ntt_external_product_decomposed(ntt_plan_t plan, void* out, const voi
   ntt_status vst = validate_words(plan, ct, (uint64_t)num_ct * comps, s, "ct");
   if (vst == NTT_OK) vst = validate_words(plan, key, rows * cols, s, "key");
   if (vst != NTT_OK) return vst;
-  if (xprod_fits(plan, (uint32_t)rows, cols, key)) {
+  if (xprod_fits(plan, kXpKindDigits, (uint32_t)rows, cols, num_ct, key)) {
     NTT_FOR_CLASSES(plan, (xprod_cls<A>(plan, c, out, ct, key, (uint32_t)rows, cols,
                                         (uint32_t)num_operands, s, comps, levels, log_base,
                                         nullptr)));
@@ -736,7 +736,7 @@ ntt_status ntt_cmux(ntt_plan_t plan, void* out, const void* acc, const uint32_t*
   ntt_status vst = validate_words(plan, acc, (uint64_t)num_ct * comps, s, "acc");
   if (vst == NTT_OK) vst = validate_words(plan, key, rows * comps, s, "key");
   if (vst != NTT_OK) return vst;
-  if (xprod_fits(plan, (uint32_t)rows, comps, key)) {
+  if (xprod_fits(plan, kXpKindCmux, (uint32_t)rows, comps, num_ct, key)) {
     NTT_FOR_CLASSES(plan, (xprod_cls<A>(plan, c, out, acc, key, (uint32_t)rows, comps,
                                         (uint32_t)(num_ct * rows), s, comps, levels, log_base,
                                         rot)));

@@ -272,6 +272,16 @@ inline uint32_t polymul_call_split(const ntt_plan_s* p, uint32_t batch) {
   return polymul_call_split(p, batch, batch);
 }
 
+// Split of a product whose rows live anywhere (polymul_rows_into; 0: none).  That
+// form has two passes, so a call that would take one at N = 2^13 runs in rows of 2^10
+// words: gathering its operands for the single pass costs more than the second trip (64
+// requests of 4 pairs over 12 limbs, 50 / 32 bits, served: 720 / 550 us gathered, 590 /
+// 460 us so).
+inline uint32_t polymul_rows_split(const ntt_plan_s* p, uint32_t batch) {
+  const uint32_t split = polymul_call_split(p, batch);
+  return split == 0 && p->log_n == 13 ? 3u : split;
+}
+
 // Polymul with a caller-provided workspace of polymul_ws_bytes(p, batch) bytes
 // (none needed when that is 0): the same launches as ntt_polymul without its
 // stream-ordered allocation.  No argument checks beyond the workspace.
@@ -282,8 +292,8 @@ ntt_status polymul_into(const ntt_plan_s* p, void* out, const void* a, const voi
 // Polymul of `batch` polynomials whose limb-rows live anywhere: row
 // poly * L + limb of a, b and out is at a_rows / b_rows / out_rows[row] (device
 // arrays of byte addresses, batch * L each).  o and ws are two contiguous
-// scratch buffers of batch * L * N words.  Only for calls whose polymul split
-// has both passes (polymul_rows_ok); the words are those of polymul_into.
+// scratch buffers of batch * L * N words.  Only for calls with a two-pass form
+// (polymul_rows_ok); the words are those of polymul_into.
 bool polymul_rows_ok(const ntt_plan_s* p, uint32_t batch);
 ntt_status polymul_rows_into(const ntt_plan_s* p, const uint64_t* out_rows, const uint64_t* a_rows,
                              const uint64_t* b_rows, uint32_t batch, void* o, void* ws,

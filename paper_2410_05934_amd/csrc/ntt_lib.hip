@@ -404,7 +404,7 @@ ntt_status polymul_into(const ntt_plan_s* plan, void* out, const void* a, const 
 }
 
 bool polymul_rows_ok(const ntt_plan_s* p, uint32_t batch) {
-  const uint32_t split = polymul_call_split(p, batch);
+  const uint32_t split = polymul_rows_split(p, batch);
   return split > 0 && split < p->log_n;
 }
 
@@ -413,7 +413,7 @@ ntt_status polymul_rows_into(const ntt_plan_s* plan, const uint64_t* out_rows, c
                              hipStream_t s) {
   if (!polymul_rows_ok(plan, batch)) return fail(NTT_EINVAL, "polymul through row tables needs two passes");
   if (!o || !ws || !out_rows || !a_rows || !b_rows) return fail(NTT_EINVAL, "null argument");
-  const uint32_t split = polymul_call_split(plan, batch);
+  const uint32_t split = polymul_rows_split(plan, batch);
   NTT_FOR_CLASSES(plan, (polymul_rows_cls<A>(plan, c, out_rows, a_rows, b_rows, o, ws, batch, split, s)));
   return NTT_OK;
 }

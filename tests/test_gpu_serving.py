@@ -213,3 +213,28 @@ def test_batched_two_pass_products_read_and_write_the_requests_in_place(flags, c
     torch.cuda.synchronize()
     for req, x in zip(reqs, da):
         assert np.array_equal(to_host(x, wb).astype(np.uint64), oracle.polymul(req[5], req[6], req[2]))
+
+
+@pytest.mark.parametrize("flags", [0, ntt.SERVER_MERGE_MODULI])
+@pytest.mark.parametrize("cls", ["f64", "u32"])
+def test_batched_products_of_2_13_run_in_place(flags, cls):
+    """N = 2^13 from 64 limb-rows on, where a product by itself takes one pass: a
+    batch still runs on the requests' own buffers, not on gathered copies."""
+    wb, primes = _CLASS_PRIMES[cls]
+    pool = primes()
+    reqs = []
+    for i in range(12):
+        L = 4 if not flags else 2 + i % 3
+        pairs = 3 + i % 2
+        a = synth.uniform_poly(7500 + 2 * i, pool[:L], pairs, 1 << 13)
+        b = synth.uniform_poly(7501 + 2 * i, pool[:L], pairs, 1 << 13)
+        reqs.append((ntt.REQ_POLYMUL, 1 << 13, pool[:L], wb, pairs, a, b))
+    got, infos, c = _run(reqs, flags, streams=1)
+    rows = {}
+    for q, x in zip(reqs, infos):
+        rows[x["launch_id"]] = rows.get(x["launch_id"], 0) + q[4] * len(q[2])
+    assert max(rows.values()) >= 64
+    batched = {x["launch_id"] for x in infos if x["batched_with"] > 1}
+    assert c["direct_launches"] == len(batched) >= 1
+    for req, g in zip(reqs, got):
+        assert np.array_equal(g, oracle.polymul(req[5], req[6], req[2]))

@@ -537,6 +537,7 @@ __global__ void __launch_bounds__(1024) bconv_ws_kernel(BconvArgs a) {
     // Output J0 + 2h + s (s = 0, 1) is finished by the lanes of half h; its
     // constants stay in registers for the whole launch.
     double cp[2], cpinv[2], cw[2], cwq[2], cs[2], csq[2];
+    constexpr bool kAhead = MODE == kBconvDown && SMAX <= 18;
 #pragma unroll
     for (int sl = 0; sl < 2; ++sl) {
       const uint32_t J = J0 + 2u * h + sl;
@@ -545,7 +546,7 @@ __global__ void __launch_bounds__(1024) bconv_ws_kernel(BconvArgs a) {
       cpinv[sl] = o[1];
       cw[sl] = o[2];
       cwq[sl] = o[3];
-      if (MODE == kBconvDown) {
+      if (kAhead) {
         const double* f = a.sf + 2u * (uint64_t)(J < a.M ? J : a.M - 1u);
         cs[sl] = f[0];
         csq[sl] = f[1];
@@ -555,7 +556,10 @@ __global__ void __launch_bounds__(1024) bconv_ws_kernel(BconvArgs a) {
     // tile ahead and so before the previous tile's stores: loads and stores
     // complete in order, and a load issued after them would wait for them.  For
     // the same reason s_J and s_J / p_J are held in registers, not read again per
-    // tile.  36 + 36 limbs of 4 x 2^16: 75 -> 72 us, 16 + 16: 33 -> 28 us.
+    // tile.  (us, loads at the start of the tile / so: 16 + 16 limbs of 4 x 2^16 25.1 /
+    // 21.5, 29 + 10 41.0 / 32.5, 36 + 36 60.6 / 55.7, 36 + 36 of 2 x 2^13 8.1 / 8.2.)
+    // With 24 k-steps the registers for it are not there (they spill: 48 + 48 limbs 109
+    // / 128), so that size loads at the start of the tile.
     auto load_sub = [&](uint32_t tile, W (&xs)[2]) {
       const uint64_t g = (uint64_t)tile * 32u + col;
 #pragma unroll
@@ -595,20 +599,39 @@ __global__ void __launch_bounds__(1024) bconv_ws_kernel(BconvArgs a) {
         const uint32_t J = J0 + 2u * h + sl;
         if (J < a.M) {
           if (MODE == kBconvDown) {
-            r = f64_sub_scale(small_to_f64((uint64_t)xs[sl]), r, cs[sl], csq[sl], cp[sl]);
+            const double s0 = kAhead ? cs[sl] : a.sf[2 * J], s1 = kAhead ? csq[sl] : a.sf[2 * J + 1];
+            r = f64_sub_scale(small_to_f64((uint64_t)xs[sl]), r, s0, s1, cp[sl]);
           }
           static_cast<W*>(a.out)[b * a.out_stride + ((uint64_t)J << a.log_n) + n] = (W)f64_to_small(r);
         }
       }
     };
-    W xn[2] = {0, 0};
-    if (MODE == kBconvDown) load_sub(first, xn);
     __syncthreads();  // the digits of the first two tiles
-    for (uint32_t t = 0; first + t < end; ++t) {
-      const W xs[2] = {xn[0], xn[1]};
-      if (MODE == kBconvDown) load_sub(first + t + 1u < end ? first + t + 1u : end - 1u, xn);
-      finish(products(buffer(t)), first + t, xs);
+    W xn[2] = {0, 0}, xo[2];
+    // One tile with its residues in `use`; the next tile's (past the run's end the
+    // last tile's again: a branch costs more) go to `ld`.
+    auto tile = [&](uint32_t t, W (&use)[2], W (&ld)[2]) {
+      if (kAhead) load_sub(first + t + 1u < end ? first + t + 1u : end - 1u, ld);
+      else if (MODE == kBconvDown) load_sub(first + t, use);
+      finish(products(buffer(t)), first + t, use);
       __syncthreads();
+    };
+    if (kAhead) load_sub(first, xn);
+    if constexpr (kAhead && SMAX <= 16) {
+      // two register sets in turn: a copy of one would wait for its loads
+      for (uint32_t t = 0; first + t < end; t += 2u) {
+        tile(t, xn, xo);
+        if (first + t + 1u < end) tile(t + 1u, xo, xn);
+      }
+    } else if constexpr (kAhead) {
+      // 18 k-steps: no registers for the second loop body
+      for (uint32_t t = 0; first + t < end; ++t) {
+        xo[0] = xn[0];
+        xo[1] = xn[1];
+        tile(t, xo, xn);
+      }
+    } else {
+      for (uint32_t t = 0; first + t < end; ++t) tile(t, xn, xo);
     }
     return;
   }

@@ -18,19 +18,24 @@ LLVM = "/opt/rocm/llvm/bin"
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """[(symbol, [instruction, ...]), ...] of every device function of the library."""
+def objects(tmp_path_factory):
+    """Paths of the library's gfx950 code objects."""
     tool = os.path.join(LLVM, "llvm-objdump")
     if not os.path.exists(tool) or not os.path.exists(ntt.library_path()):
         pytest.skip("needs the built library and llvm-objdump")
     d = tmp_path_factory.mktemp("code")
     lib = shutil.copy(ntt.library_path(), d / "libntt.so")
     subprocess.run([tool, "--offloading", lib], check=True, capture_output=True, cwd=d)
-    objs = [p for p in sorted(os.listdir(d)) if "gfx950" in p]
+    return [str(d / p) for p in sorted(os.listdir(d)) if "gfx950" in p]
+
+
+@pytest.fixture(scope="module")
+def kernels(objects):
+    """[(symbol, [instruction, ...]), ...] of every device function."""
     out = []
-    for p in objs:
-        text = subprocess.run([tool, "-d", "--no-show-raw-insn", "--no-leading-addr", p], check=True,
-                              capture_output=True, text=True, cwd=d).stdout
+    for path in objects:
+        text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn",
+                               "--no-leading-addr", path], check=True, capture_output=True, text=True).stdout
         for part in re.split(r"^(?=<\S+>:$)", text, flags=re.M)[1:]:
             head, *body = part.splitlines()
             out.append((head.strip("<>:"), [ln.split("//")[0].strip() for ln in body]))
@@ -45,3 +50,18 @@ def test_external_product_operands_load_without_branches(kernels):
     # a few per kernel (the store of the slots that hold a column), none per element
     # of a thread's 8 or 16
     assert [f for f in found if f[1] >= 8] == []
+
+
+def test_matrix_basis_conversion_keeps_its_constants_in_registers(objects):
+    """The weights-stationary kernels hold every constant operand in registers; with 24
+    k-steps ModDown has a few words of scratch (20 bytes over 64-bit words: 109 us on 48 + 48 limbs of
+    4 x 2^16; at 36 bytes 128)."""
+    seen = 0
+    for path in objects:
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", path], check=True,
+                               capture_output=True, text=True).stdout
+        for name, size in re.findall(r"\.name:\s+(\S*bconv_ws_kernel\S*)\s.*?\.private_segment_fixed_size:\s+(\d+)",
+                                     notes, flags=re.S):
+            seen += 1
+            assert int(size) <= (28 if "Li24E" in name else 0), (name, size)
+    assert seen == 48  # 2 word widths, 4 sizes, 2 pairs per helper thread, 3 modes

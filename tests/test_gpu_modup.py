@@ -175,3 +175,25 @@ def test_rejects_overlap_and_bad_sizes():
     with pytest.raises(ntt.NTTError) as ei:
         ntt.BasisExtension(N, q, [q[0]], 64)
     assert ei.value.name == "NTT_EINVAL"
+
+
+@pytest.mark.parametrize("word_bits", [32, 64])
+@pytest.mark.parametrize("K", [10, 16, 24, 34, 48])
+def test_mod_down_over_every_run_length_of_tiles(word_bits, K):
+    """Matrix form with its residues a tile ahead: runs of one to a few tiles per
+    workgroup, odd and even, whole and cut off by the end, at each of its sizes (8,
+    16, 18 and 24 k-steps); against the vector form, and the oracle on one polynomial."""
+    L, N = 5, 1 << 12
+    q, p = _bases(word_bits, L, K)
+    down = {m: ntt.BasisExtension(N, q, p, word_bits, mfma=m) for m in (True, False)}
+    one = synth.uniform_poly(800 + K, q + p, 1, N)
+    for batch in (1, 3, 5, 9, 14):
+        x = to_device(np.concatenate([synth.uniform_poly(810 + K, q + p, 1, N)] * (batch - 1) + [one]), word_bits)
+        x[:-1] = x[:-1].roll(batch, dims=2)
+        out = {}
+        for m, d in down.items():
+            out[m] = empty_device((batch, L, N), word_bits)
+            d.mod_down(out[m], x)
+        torch.cuda.synchronize()
+        assert torch.equal(out[True], out[False])
+        assert np.array_equal(to_host(out[True][-1:], word_bits).astype(np.uint64), oracle.mod_down(one, q, p))

@@ -191,7 +191,7 @@ ntt_status ntt_pointwise_mac(ntt_plan_t plan, void* acc, const void* a, const vo
 typedef struct ntt_bconv_s* ntt_bconv_t;
 /* When every modulus is below 2^50 - 2^10, N >= 32 and there are more than 8
  * source moduli the sum runs on the int8 matrix cores (balanced base-256 digits,
- * exact int32 sums; up to 8 sources, and up to 12 in large ModDown calls, the
+ * exact int32 sums; up to 8 sources, and in large calls with few targets, the
  * vector units are faster; beyond 48 moduli on a side the matrix cores are taken
  * from 16 moduli on both sides).  NTT_BCONV_NO_MFMA keeps it on the vector
  * units, NTT_BCONV_MFMA takes the matrix cores at any L and M (the fp64 bound

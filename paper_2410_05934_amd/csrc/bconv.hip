@@ -65,6 +65,7 @@ struct ntt_bconv_s {
   double* d_f3 = nullptr;    // [M][2 + 2 few]: p_j, 1/p_j, then per source (Q/q_i) mod p_j and that
                              // over p_j (zeros past the last source)
   bool mfma = false;         // fp64-eligible, N >= 32, not switched off: int8 MFMA form
+  bool mfma_forced = false;  // NTT_BCONV_MFMA: at any size
   uint64_t* d_kop = nullptr; // MFMA constant operands [ceil(M/4)][ceil(L/2)][64 lanes]
   double* d_om = nullptr;    // [M][8][2]: 256^c mod p_j and that over p_j
   double* d_om2 = nullptr;   // [M][4]: p_j, 1/p_j, 2^32 mod p_j, that over p_j
@@ -92,7 +93,6 @@ struct BconvArgs {
   const double* f1;
   const double* f2;
   const double* fp;
-  const double* f3;
   const uint64_t* kop;
   const double* om;
   const double* om2;
@@ -108,6 +108,7 @@ struct BconvArgs {
   uint64_t aux_stride;
   const uint64_t* sc;    // [M][2]: s_j and floor(s_j 2^64 / p_j)   (ModDown)
   const double* sf;      // [M][2]: s_j and s_j / p_j               (ModDown)
+  const double* f3;     // the few-source kernel's constants (last: the others' stay where they were)
 };
 
 // What a conversion kernel does around the sum (the template argument MODE).
@@ -938,6 +939,7 @@ static ntt_status bconv_build(ntt_bconv_s** out, uint32_t N, const uint64_t* src
                         !(flags & NTT_BCONV_NO_WS);
   h->mfma = h->f64 && N >= 32 && !(flags & NTT_BCONV_NO_MFMA) &&
             ((flags & NTT_BCONV_MFMA) || (ws_shape ? L > 8 : L >= 16 && M >= 16));
+  h->mfma_forced = (flags & NTT_BCONV_MFMA) != 0;
   h->few = h->f64 && !(flags & NTT_BCONV_MFMA) ? few_size(L) : 0u;
   if (h->few && e == hipSuccess) {
     const size_t stride = 2 + 2 * (size_t)h->few;
@@ -1016,6 +1018,27 @@ static ntt_status bconv_build(ntt_bconv_s** out, uint32_t N, const uint64_t* src
   return NTT_OK;
 }
 
+// Whether a call whose shape the matrix cores take by default (more than 8 sources)
+// still runs on the vector units: with few targets the matrix form's one or two owner
+// waves finish every output while its digit waves wait, and large calls fill the chip
+// without it.  Vector over matrix time:
+//   up to 16 sources (few-source kernel): up to 4 targets from 2^15 coefficients per
+//     target on (conversion from 9 / 16 sources, 4 x 2^16 coefficients: 1 target 0.47 /
+//     0.62, 4 0.68 / 0.90; 2^14: 1.05 / 1.37, 1.44 / 1.93), and up to 8 targets of up
+//     to 10 sources from 3 x 2^16 on (9 sources, 8 targets 0.81, ModUp 0.89); ModDown, whose outputs cost
+//     the owners more, up to 8 targets from 2^16 coefficients on (4 x 2^16: 8 targets
+//     0.75 / 1.05, 12 0.98 / 1.32; 2^15: 1.13 / 1.46);
+//   more sources, ModDown from 3 x 2^16 coefficients on (the kernel that re-reads them):
+//     17 sources 0.64 .. 0.94 for 1 .. 4 targets, 24 0.96 / 1.03 / 1.34 for 1 / 2 / 4,
+//     36 1.13 / 1.54 for 1 / 4; above 36, where the matrix form cannot load ahead, 4 x
+//     2^16: 0.74 / 0.93 for 1 / 4.
+inline bool vector_first(int mode, bool few, uint32_t L, uint32_t M, uint32_t total) {
+  if (few)
+    return (M <= 4 && total >= M << 15) ||
+           (M <= 8 && total >= (mode == kBconvDown ? 1u << 16 : L <= 10 ? 3u << 16 : ~0u));
+  return mode == kBconvDown && total >= 3u << 16 && (L > 36 ? M <= 4 : L <= 24 && L * M <= 68);
+}
+
 // One launch of conversion h over `batch` polynomials in the given mode; the
 // caller has checked pointers, sizes and overlaps.
 static ntt_status bconv_run(const ntt_bconv_s* h, int mode, void* out, uint64_t out_stride,
@@ -1047,13 +1070,10 @@ static ntt_status bconv_run(const ntt_bconv_s* h, int mode, void* out, uint64_t 
   a.sc = sc;
   a.sf = sf;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // ModDown's extra work per output falls on the few owner waves of the matrix
-  // form: on large calls the vector form stays ahead up to 12 sources (us, vector /
-  // matrix: 29 + 10 limbs of 4 x 2^16 42 / 52, 36 + 12 54 / 57; 29 + 10 of 3 x 2^15
-  // 20 / 17).
-  const bool few_first = !h->mfma || (mode == kBconvDown && h->L <= 12 && a.total >= (1u << 18));
-  const uint32_t few = few_first ? h->few : 0u;
-  const bool mfma = h->mfma && !few;
+  const bool vector = !h->mfma || (!h->mfma_forced &&
+                                   vector_first(mode, h->few != 0, h->L, h->M, a.total));
+  const uint32_t few = vector ? h->few : 0u;
+  const bool mfma = h->mfma && !vector;
   // weights-stationary grid: every workgroup that fits at once, at most one per tile
   const uint32_t tiles = a.total >> 5;
   const uint32_t ws_grid = h->ws_grid ? (tiles < h->ws_grid ? tiles : h->ws_grid) : 0u;

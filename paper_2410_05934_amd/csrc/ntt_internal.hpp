@@ -264,15 +264,18 @@ inline uint32_t call_split(const ntt_plan_s* p, uint32_t batch) {
 // rows 20 / 18 against 23 / 19, 144 21 / 19 against 35 / 26), below that in rows of
 // 2^10 words (8 rows 15 / 10 against 17 / 13), and 2^14 in rows of 2^10 words (144
 // rows 43 / 33 against 47 / 37).
-inline uint32_t polymul_call_split(const ntt_plan_s* p, uint32_t batch, uint32_t table_batch) {
-  if (p->forced_split >= 0) return polymul_split_log(p->log_n, (uint32_t)p->forced_split);
-  const uint32_t cls = (uint32_t)dominant_class(p);
-  const uint32_t tuned = tuned_split_for(p->log_n, cls, (uint64_t)table_batch * p->L, ~0u);
+// (polymul_tuned_split: the rule for a given table entry, ~0u for none.)
+inline uint32_t polymul_tuned_split(const ntt_plan_s* p, uint32_t batch, uint32_t tuned) {
   if (tuned != ~0u && !(tuned == 0 && p->log_n == 14)) return polymul_split_log(p->log_n, tuned);
-  if (!p->size_split || cls == 2 || p->log_n < 13 || p->log_n > 14)
+  if (!p->size_split || dominant_class(p) == 2 || p->log_n < 13 || p->log_n > 14)
     return polymul_split_log(p->log_n, p->log_n1);
   if (p->log_n == 13) return (uint64_t)batch * p->L >= 64 ? 0u : 3u;
   return 4;
+}
+inline uint32_t polymul_call_split(const ntt_plan_s* p, uint32_t batch, uint32_t table_batch) {
+  if (p->forced_split >= 0) return polymul_split_log(p->log_n, (uint32_t)p->forced_split);
+  return polymul_tuned_split(p, batch, tuned_split_for(p->log_n, (uint32_t)dominant_class(p),
+                                                       (uint64_t)table_batch * p->L, ~0u));
 }
 inline uint32_t polymul_call_split(const ntt_plan_s* p, uint32_t batch) {
   return polymul_call_split(p, batch, batch);

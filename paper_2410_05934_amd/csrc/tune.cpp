@@ -11,7 +11,8 @@
 // (16, 8 or 4 values per thread: the threads per chunk, the paper's threads per
 // block) per direction and records the fastest; at the chosen split and radices
 // it times column passes of 256, 128 and 64 columns per workgroup (4, 2 or 1
-// waves; one thread per column), then polymul rows of both radices.  Calls
+// waves; one thread per column), then polymul rows of both radices at the split that
+// products take beside that entry.  Calls
 // without a forced split look the keys up (the nearest recorded row bucket
 // within two powers of two), else use the defaults.  The row pass's LDS padding
 // is fixed (one spare slot per 16 words): its bank conflicts are measured at
@@ -260,12 +261,19 @@ ntt_status ntt_tune_split(uint32_t N, const uint64_t* moduli, uint32_t num_modul
     }
     best_cb_us = bc;
   }
-  // Polymul rows at the chosen split: radix-16 against radix-8 (b aliases a; out
-  // is a second buffer).  Skipped when that buffer cannot be had.
+  // Polymul rows, radix-16 against radix-8, at the split products take with this
+  // entry (b aliases a; out is a second buffer).  Skipped when that buffer cannot be had.
   uint32_t best_rb_pm = 0;
+  uint32_t pm_split = 0;
   if (st == NTT_OK && any) {
-    // polymul's own split rule: its rows are at most 2^13 words
-    const uint32_t pm_split = polymul_split_log((uint32_t)log_n, best_split);
+    ntt_plan_t p = nullptr;
+    st = ntt_plan_create(&p, N, moduli, num_moduli, word_bits, 0);
+    if (st == NTT_OK) {
+      pm_split = polymul_tuned_split(p, batch, best_split);
+      ntt_plan_destroy(p);
+    }
+  }
+  if (st == NTT_OK && any) {
     const int n2 = log_n - (int)pm_split;
     void* out = nullptr;
     if (n2 >= 10 && n2 <= 13 && hipMalloc(&out, bytes) == hipSuccess) {
@@ -273,7 +281,7 @@ ntt_status ntt_tune_split(uint32_t N, const uint64_t* moduli, uint32_t num_modul
       for (int rb : {4, 3}) {
         ntt_plan_t p = nullptr;
         st = ntt_plan_create(&p, N, moduli, num_moduli, word_bits,
-                             NTT_FLAG_SPLIT(best_split) | (rb == 3 ? NTT_FLAG_ROW_RADIX8 : 0u));
+                             NTT_FLAG_SPLIT(pm_split) | (rb == 3 ? NTT_FLAG_ROW_RADIX8 : 0u));
         if (st != NTT_OK) break;
         if (rb == 4) p->row_rb = 4;
         for (int w = 0; w < 2 && st == NTT_OK; ++w) st = ntt_polymul(p, out, buf, buf, batch, s);

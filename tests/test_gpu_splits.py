@@ -72,3 +72,33 @@ def test_few_rows_of_2_13(cls, rows, split):
     word = lambda t: to_host(t, wb).astype(np.uint64)  # noqa: E731
     assert np.array_equal(word(f), oracle.forward(word(a), mods))
     assert np.array_equal(word(i), oracle.inverse(word(a), mods))
+
+
+@pytest.mark.parametrize("cls,logn,batch", [("fp64", 14, 48), ("fp64", 13, 40), ("i64", 14, 2),
+                                            ("fp64", 15, 2)])
+def test_tuner_times_the_product_rows_that_calls_run(cls, logn, batch):
+    """The radix the tuner records for products is that of the rows products take with
+    the recorded split (N = 2^14 in one pass, which products do not have, included)."""
+    bits, wb = PRIMES[cls]
+    N, mods = 1 << logn, synth.primes_below(1 << bits, 1 << 17, 3)
+
+    def product_rows(run):
+        ntt.stats_reset()
+        ntt.stats_enable(True)
+        try:
+            run()
+            torch.cuda.synchronize()
+            return {n for n in ntt.stats_collect() if n.startswith("polymul_row")}
+        finally:
+            ntt.stats_enable(False)
+            ntt.stats_reset()
+
+    ntt.tune_clear()
+    try:
+        timed = product_rows(lambda: ntt.tune_split(N, mods, wb, batch))
+        plan = ntt.Plan(N, mods, wb)
+        a = torch.randint(0, mods[-1], (batch, 3, N), device="cuda")
+        taken = product_rows(lambda: plan.polymul(torch.empty_like(a), a, a))
+    finally:
+        ntt.tune_clear()
+    assert len(timed) == 2 and len(taken) == 1 and taken <= timed

@@ -502,15 +502,19 @@ def _stream_handle(stream) -> int:
 
 def _workspace(nbytes: int, device, stream):
     """Scratch that torch's allocator hands out on the call's stream (its memory is
-    reused only in that stream's order), or None: under graph capture or out of memory."""
+    reused only in that stream's order), or None (the library allocates): under graph
+    capture, out of memory, and on a stream that is not torch's own, whose handle may
+    end and return while the allocator still keeps blocks under it."""
     import torch
+    if torch.cuda.is_current_stream_capturing():
+        return None
     try:
-        if stream is not None:
-            with torch.cuda.stream(stream):
-                return _workspace(nbytes, device, None)
-        if torch.cuda.is_current_stream_capturing():
+        if stream is None:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        if type(stream) is not torch.cuda.Stream:
             return None
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        with torch.cuda.stream(stream):
+            return _workspace(nbytes, device, None)
     except torch.OutOfMemoryError:
         return None
 

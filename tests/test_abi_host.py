@@ -179,3 +179,16 @@ def test_tuning_table_round_trips_on_the_host(tmp_path):
         assert ei.value.name == "NTT_EINVAL"
     finally:
         ntt.tune_clear()
+
+
+def test_product_workspace_takes_any_object_with_a_stream_handle(monkeypatch):
+    """Every call takes any object with `cuda_stream`; only torch's own streams get a
+    workspace from torch's allocator, and none while a stream is captured."""
+    torch = pytest.importorskip("torch")
+    import types
+    capturing = [False]
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing[0])
+    assert ntt._workspace(16, "cpu", types.SimpleNamespace(cuda_stream=5)) is None
+    assert ntt._workspace(16, "cpu", None).numel() == 16
+    capturing[0] = True
+    assert ntt._workspace(16, "cpu", None) is None

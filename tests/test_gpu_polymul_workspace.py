@@ -42,3 +42,25 @@ def test_product_workspace_from_the_caller():
     plan.polymul(out, a, b, stream=side)
     side.synchronize()
     assert torch.equal(out, want)
+
+
+def test_product_on_any_object_with_a_stream_handle():
+    """A two-pass product takes what every other call takes as its stream."""
+    mods = synth.primes_below(1 << 50, 1 << 17, 2)
+    N = 1 << 15
+    plan = ntt.Plan(N, mods, 64)
+    a = torch.randint(0, mods[-1], (1, 2, N), device="cuda")
+    b = torch.randint(0, mods[-1], (1, 2, N), device="cuda")
+    want = plan.polymul(torch.empty_like(a), a, b)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+
+    class Handle:
+        cuda_stream = side.cuda_stream
+
+    for stream in (Handle(), torch.cuda.ExternalStream(side.cuda_stream)):
+        out = torch.zeros_like(a)
+        side.wait_stream(torch.cuda.current_stream())
+        plan.polymul(out, a, b, stream=stream)
+        side.synchronize()
+        assert torch.equal(out, want)

@@ -338,7 +338,8 @@ ntt_status ntt_polymul(ntt_plan_t plan, void* out, const void* a, const void* b,
 
 /* ntt_polymul with the two-pass workspace from the caller: *bytes of
  * ntt_polymul_workspace (0 for a single-pass product) at ws, device memory that
- * nothing else uses until the stream has passed the call.  The pool allocation
+ * nothing else uses until the stream has passed the call, aligned to the plan's
+ * words and apart from out, a and b (else NTT_EINVAL).  The pool allocation
  * and release of ntt_polymul cost the host some 15 us a call; a caller with an
  * allocator of its own (the Python binding) passes a block here.  With ws null or
  * too small the call allocates as ntt_polymul does. */

@@ -808,11 +808,21 @@ ntt_status ntt_polymul_ws(ntt_plan_t plan, void* out, const void* a, const void*
   if (st != NTT_OK) return st;
   if (!out || !a || !b) return fail(NTT_EINVAL, "null data");
   if (out == a || out == b) return fail(NTT_EINVAL, "out must not alias a or b");
+  const size_t bytes = polymul_ws_bytes(plan, batch);
+  const bool given = bytes && ws && ws_bytes >= bytes;
+  if (given) {
+    // the workspace is as large as each operand; the kernels access it by words
+    const uintptr_t w = reinterpret_cast<uintptr_t>(ws);
+    if (w % (plan->word_bits / 8)) return fail(NTT_EINVAL, "ws must be aligned to the plan's words");
+    for (const void* x : {static_cast<const void*>(out), a, b}) {
+      const uintptr_t p = reinterpret_cast<uintptr_t>(x);
+      if (w < p + bytes && p < w + bytes) return fail(NTT_EINVAL, "ws must not overlap out, a or b");
+    }
+  }
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = validate_words(plan, a, batch, s, "a")) != NTT_OK) return st;
   if ((st = validate_words(plan, b, batch, s, "b")) != NTT_OK) return st;
-  const size_t bytes = polymul_ws_bytes(plan, batch);
-  if (!bytes || (ws && ws_bytes >= bytes)) return polymul_into(plan, out, a, b, batch, ws, s);
+  if (!bytes || given) return polymul_into(plan, out, a, b, batch, given ? ws : nullptr, s);
   void* own = nullptr;
   hipError_t e = hipMallocAsync(&own, bytes, s);
   if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(polymul workspace)");

@@ -64,3 +64,21 @@ def test_product_on_any_object_with_a_stream_handle():
         plan.polymul(out, a, b, stream=stream)
         side.synchronize()
         assert torch.equal(out, want)
+
+
+def test_workspace_that_overlaps_or_is_misaligned_is_refused():
+    """Before any launch, and only where the call would use it."""
+    mods = synth.primes_below(1 << 50, 1 << 17, 1)
+    N = 1 << 15
+    plan = ntt.Plan(N, mods, 64)
+    block = torch.zeros((4, N), dtype=torch.int64, device="cuda")
+    a, b, out, ws = (block[i] for i in range(4))
+    bad = ntt.lib().ntt_polymul_ws
+    stream, size = torch.cuda.current_stream().cuda_stream, N * 8
+    for ptr in (a.data_ptr(), b.data_ptr(), out.data_ptr(), out.data_ptr() + 8, ws.data_ptr() - 8,
+                ws.data_ptr() + 4):
+        assert bad(plan._h, out.data_ptr(), a.data_ptr(), b.data_ptr(), 1, ptr, size, stream) == 1
+    assert bad(plan._h, out.data_ptr(), a.data_ptr(), b.data_ptr(), 1, ws.data_ptr(), size, stream) == 0
+    # too small: not used, so not looked at
+    assert bad(plan._h, out.data_ptr(), a.data_ptr(), b.data_ptr(), 1, ws.data_ptr() + 4, 8, stream) == 0
+    torch.cuda.synchronize()

@@ -49,6 +49,7 @@
 #include <vector>
 
 #include "ntt_internal.hpp"
+#include "bconv_rules.hpp"
 #include "numtheory.hpp"
 
 struct ntt_bconv_s {
@@ -111,12 +112,6 @@ struct BconvArgs {
   const double* f3;     // the few-source kernel's constants (last: the others' stay where they were)
 };
 
-// What a conversion kernel does around the sum (the template argument MODE).
-constexpr int kBconvPlain = 0;  // y_j
-constexpr int kBconvUp = 1;     // y_j, and the source residues copied beside them
-constexpr int kBconvDown = 2;   // (x_j - y_j) s_j mod p_j
-
-constexpr uint32_t kBconvBlock = 256;
 
 // y w mod q up to one q: y w - floor(y ws / 2^64) q lies in [0, 2q) for any
 // 64-bit y when w < q < 2^63 and ws = floor(w 2^64 / q).
@@ -271,7 +266,6 @@ __device__ __forceinline__ W f64_to_word(double r) {
 // 7 S + 25 operations per output, below the memory time up to about 10 sources.
 // Measured (ModDown, above form -> this): 36 + 4 limbs of 4 x 2^16 56.7 -> 35.6 us
 // (5.0 TB/s, the copy rate), 24 + 8 53.3 -> 32.6 us, 20 + 5 34.1 -> 21.2 us.
-constexpr int kFewUnroll = 4;
 
 template <class W, int S, int MODE>
 __global__ void __launch_bounds__(kBconvBlock) bconv_few_kernel(BconvArgs a, uint32_t per) {
@@ -330,26 +324,14 @@ __global__ void __launch_bounds__(kBconvBlock) bconv_few_kernel(BconvArgs a, uin
   }
 }
 
-// Grid rows of the few-source kernel: enough to put about eight waves on every
-// SIMD when one coefficient per thread does not, each row at least kFewUnroll
-// targets.  (ModDown 24 + 8 limbs of 4 x 2^16: 37.2 us with four waves, 32.6 with
-// eight, 35.0 with sixteen.)
-inline uint32_t few_rows(uint32_t total, uint32_t M) {
-  const uint32_t want = (uint32_t)((2048ull * 256u + total - 1u) / total);
-  const uint32_t most = (M + kFewUnroll - 1) / kFewUnroll;
-  return want < 1u ? 1u : want < most ? want : most;
-}
-
 template <class W, int S, int MODE>
 static hipError_t launch_few_n(const BconvArgs& a, hipStream_t s) {
-  const uint32_t rows = few_rows(a.total, a.M), per = (a.M + rows - 1) / rows;
-  const dim3 grid((a.total + kBconvBlock - 1) / kBconvBlock, (a.M + per - 1) / per);
+  const FewGrid g = few_grid(a.total, a.M);
+  const dim3 grid(g.blocks, g.rows);
+  const uint32_t per = g.per;
   hipLaunchKernelGGL((bconv_few_kernel<W, S, MODE>), grid, dim3(kBconvBlock), 0, s, a, per);
   return hipGetLastError();
 }
-
-// Register sizes the few-source kernel is built for.
-inline uint32_t few_size(uint32_t L) { return L <= 8 ? L : L <= 16 ? (L + 1u) & ~1u : 0u; }
 
 template <class W, int MODE>
 static hipError_t launch_few(const BconvArgs& a, uint32_t size, hipStream_t s) {
@@ -1016,27 +998,6 @@ static ntt_status bconv_build(ntt_bconv_s** out, uint32_t N, const uint64_t* src
   }
   *out = h;
   return NTT_OK;
-}
-
-// Whether a call whose shape the matrix cores take by default (more than 8 sources)
-// still runs on the vector units: with few targets the matrix form's one or two owner
-// waves finish every output while its digit waves wait, and large calls fill the chip
-// without it.  Vector over matrix time:
-//   up to 16 sources (few-source kernel): up to 4 targets from 2^15 coefficients per
-//     target on (conversion from 9 / 16 sources, 4 x 2^16 coefficients: 1 target 0.47 /
-//     0.62, 4 0.68 / 0.90; 2^14: 1.05 / 1.37, 1.44 / 1.93), and up to 8 targets of up
-//     to 10 sources from 3 x 2^16 on (9 sources, 8 targets 0.81, ModUp 0.89); ModDown, whose outputs cost
-//     the owners more, up to 8 targets from 2^16 coefficients on (4 x 2^16: 8 targets
-//     0.75 / 1.05, 12 0.98 / 1.32; 2^15: 1.13 / 1.46);
-//   more sources, ModDown from 3 x 2^16 coefficients on (the kernel that re-reads them):
-//     17 sources 0.64 .. 0.94 for 1 .. 4 targets, 24 0.96 / 1.03 / 1.34 for 1 / 2 / 4,
-//     36 1.13 / 1.54 for 1 / 4; above 36, where the matrix form cannot load ahead, 4 x
-//     2^16: 0.74 / 0.93 for 1 / 4.
-inline bool vector_first(int mode, bool few, uint32_t L, uint32_t M, uint32_t total) {
-  if (few)
-    return (M <= 4 && total >= M << 15) ||
-           (M <= 8 && total >= (mode == kBconvDown ? 1u << 16 : L <= 10 ? 3u << 16 : ~0u));
-  return mode == kBconvDown && total >= 3u << 16 && (L > 36 ? M <= 4 : L <= 24 && L * M <= 68);
 }
 
 // One launch of conversion h over `batch` polynomials in the given mode; the

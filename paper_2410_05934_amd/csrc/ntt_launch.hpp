@@ -8,6 +8,7 @@
 #include "fused.hpp"
 #include "ntt_internal.hpp"
 #include "ntt_kernels.hpp"
+#include "once_device.hpp"
 #include "xprod.hpp"
 
 namespace nttk {
@@ -461,6 +462,29 @@ hipError_t mac_cls(const ntt_plan_s* p, int c, void* out, const void* a, const v
   return hipGetLastError();
 }
 
+// Past 64 KiB of LDS a kernel has to be allowed its size.  That limit belongs to the
+// kernel, not to a launch, so every call sets the largest size any launch has (rows * N
+// is at most 2^14): with a call's own size a smaller call of another thread could lower
+// it between a larger call's setting and its launch.
+constexpr int kXprodMaxLds = (1 << 14) * 17 / 16 * 8;
+static_assert(kXprodMaxLds <= (int)kXprodLds, "more LDS than a compute unit has");
+template <void (*K)(XpArgs)>
+hipError_t launch_xprod_k(dim3 grid, dim3 block, size_t lds, const XpArgs& x, hipStream_t s) {
+  if (lds > 65536) {
+    static OncePerDevice allowed;
+    int device = -1;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess)
+      e = allowed.run(device, [] {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(K),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, kXprodMaxLds);
+      });
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(K, grid, block, lds, s, x);
+  return hipGetLastError();
+}
+
 template <class A, int LOGN2>
 hipError_t launch_xprod_n(const XpArgs& x, uint32_t groups, hipStream_t s) {
   // Radix-8 slots (twice the threads, half the butterflies per thread) when the
@@ -473,25 +497,16 @@ hipError_t launch_xprod_n(const XpArgs& x, uint32_t groups, hipStream_t s) {
   LaunchTimer t(x.rot ? "cmux" : x.levels ? "xprod_dec" : "xprod", A::kName, LOGN2, false, false,
                 ((uint64_t)groups * x.cols * x.n_cls) << LOGN2, s);
   const dim3 grid(groups * x.n_cls), block(threads);
-  auto go = [&](auto kernel) -> hipError_t {
-    if (lds > 65536) {
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(kernel, grid, block, lds, s, x);
-    return hipGetLastError();
-  };
   if constexpr (LOGN2 >= 10) {
     if (r8) {
-      if (x.rot) return go(xprod_kernel<A, LOGN2, kXpCmux, 3>);
-      if (x.levels) return go(xprod_kernel<A, LOGN2, kXpDecompose, 3>);
-      return go(xprod_kernel<A, LOGN2, kXpOperands, 3>);
+      if (x.rot) return launch_xprod_k<xprod_kernel<A, LOGN2, kXpCmux, 3>>(grid, block, lds, x, s);
+      if (x.levels) return launch_xprod_k<xprod_kernel<A, LOGN2, kXpDecompose, 3>>(grid, block, lds, x, s);
+      return launch_xprod_k<xprod_kernel<A, LOGN2, kXpOperands, 3>>(grid, block, lds, x, s);
     }
   }
-  if (x.rot) return go(xprod_kernel<A, LOGN2, kXpCmux>);
-  if (x.levels) return go(xprod_kernel<A, LOGN2, kXpDecompose>);
-  return go(xprod_kernel<A, LOGN2, kXpOperands>);
+  if (x.rot) return launch_xprod_k<xprod_kernel<A, LOGN2, kXpCmux>>(grid, block, lds, x, s);
+  if (x.levels) return launch_xprod_k<xprod_kernel<A, LOGN2, kXpDecompose>>(grid, block, lds, x, s);
+  return launch_xprod_k<xprod_kernel<A, LOGN2, kXpOperands>>(grid, block, lds, x, s);
 }
 
 // comps / levels / log_base: the operands are the digits of ciphertexts in `a`

@@ -73,3 +73,35 @@ def test_digits_and_cmux(bits, wb, logn, comps, levels, digits, cmux):
                           oracle.external_product_decomposed(acc, key, mods, levels, beta, comps))
     assert np.array_equal(to_host(out, wb).astype(np.uint64),
                           oracle.cmux(acc, key, mods, rot, levels, beta))
+
+
+def test_threads_with_workgroups_of_different_sizes():
+    """One kernel from two threads, workgroups of 77 and 136 KiB of LDS by turns."""
+    import threading
+    N, cols, mods = 1 << 10, 1, synth.primes_below(1 << 32, 1 << 17, 1)
+    plan = ntt.Plan(N, mods, 32)
+    cases = {}
+    for rows in (9, 16):
+        ops = synth.uniform_poly(31 + rows, mods, rows, N)
+        key = synth.uniform_poly(32 + rows, mods, rows, N).reshape(rows, 1, 1, N)
+        mac = oracle.mac(oracle.forward(ops, mods), key, mods, rows, cols)
+        cases[rows] = (to_device(ops, 32), to_device(key, 32),
+                       oracle.inverse(np.asarray(mac).reshape(-1, 1, N), mods), empty_device((1, 1, 1, N), 32))
+    torch.cuda.synchronize()
+    errors = []
+
+    def work(rows):
+        da, dk, _, out = cases[rows]
+        try:
+            for _ in range(200):
+                plan.external_product(out, da, dk, rows, cols)
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(r,)) for r in cases]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    torch.cuda.synchronize()
+    assert not errors
+    for _, _, want, out in cases.values():
+        assert np.array_equal(to_host(out, 32).astype(np.uint64).reshape(-1, 1, N), want)

@@ -213,8 +213,6 @@ struct ntt_server_s {
   ntt_server_counters ctr{};
   std::thread th;
 
-  uint32_t* d_iota = nullptr;  // 0, 1, ..., kMaxMergedLimbs - 1: the limb list of a merged launch
-
   bool serial() const { return flags & NTT_SERVER_SERIAL; }
   bool dry() const { return flags & NTT_SERVER_DRY_RUN; }
   bool merging() const { return !serial() && (flags & NTT_SERVER_MERGE_MODULI); }
@@ -265,13 +263,13 @@ struct ntt_server_s {
     // A launch over requests of different moduli runs one polynomial of a
     // virtual plan whose limbs are every request's limbs, polynomial by
     // polynomial, in gather order.  Its host constants are concatenated here;
-    // its device constants are gathered into the arena with the operands.
+    // its device constants are gathered into the arena with the operands.  All limbs
+    // are of one class, so its launches take no limb list.
     ntt_plan_s vp;
     std::vector<const ntt_plan_s*> src_plans;
     ntt_plan_t run = plan;
     uint32_t run_batch = polys;
     if (mixed) {
-      if (!d_iota) return fail(NTT_ENOMEM, "server limb list missing");
       vp.device = plan->device;
       vp.N = plan->N;
       vp.log_n = plan->log_n;
@@ -294,7 +292,6 @@ struct ntt_server_s {
       vp.cls_cnt[c] = vp.L;
       vp.h_cls_limbs.resize(vp.L);
       for (uint32_t l = 0; l < vp.L; ++l) vp.h_cls_limbs[l] = l;
-      vp.d_cls_limbs = d_iota;
       run = &vp;
       run_batch = 1;
     }
@@ -655,16 +652,8 @@ ntt_status ntt_server_create(ntt_server_t* out, uint64_t budget_bytes, uint32_t 
       e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
       if (e == hipSuccess) s->streams.push_back(st);
     }
-    if (e == hipSuccess) {
-      std::vector<uint32_t> iota(kMaxMergedLimbs);
-      for (uint32_t i = 0; i < kMaxMergedLimbs; ++i) iota[i] = i;
-      e = hipMalloc(&s->d_iota, kMaxMergedLimbs * sizeof(uint32_t));
-      if (e == hipSuccess)
-        e = hipMemcpy(s->d_iota, iota.data(), kMaxMergedLimbs * sizeof(uint32_t), hipMemcpyHostToDevice);
-    }
     if (e != hipSuccess) {
       for (hipStream_t st : s->streams) (void)hipStreamDestroy(st);
-      if (s->d_iota) (void)hipFree(s->d_iota);
       delete s;
       return hip_fail(e, "server streams");
     }
@@ -802,7 +791,6 @@ ntt_status ntt_server_destroy(ntt_server_t s) {
     if (a) (void)hipFree(a);
   for (hipEvent_t ev : s->free_events) (void)hipEventDestroy(ev);
   for (auto& kv : s->plans) ntt_plan_destroy(kv.second);
-  if (s->d_iota) (void)hipFree(s->d_iota);
   for (hipStream_t st : s->streams) (void)hipStreamDestroy(st);
   delete s;
   return NTT_OK;

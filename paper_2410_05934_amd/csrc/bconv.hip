@@ -171,23 +171,6 @@ __global__ void __launch_bounds__(kBconvBlock) bconv_kernel(BconvArgs a) {
   }
 }
 
-// x w mod q for x, w < q < 2^50 - 2^10 given wq = w/q: the exact value of
-// x w - c q with c the rounded quotient, in (-7/8 q, 7/8 q).
-__device__ __forceinline__ double f64_mulmod_pre(double x, double w, double wq, double q) {
-  const double h = x * w;
-  const double l = __builtin_fma(x, w, -h);
-  const double c = __builtin_rint(x * wq);
-  return __builtin_fma(-c, q, h) + l;
-}
-
-// The ModDown step on a reduced sum r in [0, p): (x - r) s mod p for the
-// residue x in [0, p), with s < p < 2^50 - 2^10 and sq = s / p.  |x - r| < p,
-// so the product is exact as for non-negative operands.
-__device__ __forceinline__ double f64_sub_scale(double x, double r, double s, double sq, double p) {
-  const double v = f64_mulmod_pre(x - r, s, sq, p);
-  return v < 0.0 ? v + p : v;
-}
-
 template <class W, int MODE>
 __global__ void __launch_bounds__(kBconvBlock) bconv_f64_kernel(BconvArgs a) {
   constexpr int JB = kBconvChunk;

@@ -69,6 +69,23 @@ NTT_HD uint64_t mulhi64(uint64_t a, uint64_t b) {
 #endif
 }
 
+// One device instruction each; everything built on them is the same code on both sides.
+NTT_HD uint32_t mulhi32(uint32_t a, uint32_t b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __umulhi(a, b);
+#else
+  return (uint32_t)(((uint64_t)a * b) >> 32);
+#endif
+}
+// Low 32 bits of (hi 2^32 + lo) >> (s mod 32).
+NTT_HD uint32_t funnel32(uint32_t hi, uint32_t lo, uint32_t s) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_alignbit(hi, lo, s);
+#else
+  return (uint32_t)((((uint64_t)hi << 32) | lo) >> (s & 31u));
+#endif
+}
+
 constexpr double kTwo52 = 4503599627370496.0;  // 2^52
 
 // Largest modulus (exclusive) of the ArF64L class.  Four inverse (GS) stages
@@ -92,6 +109,23 @@ NTT_HD double f64_mulmod(double x, double w, double q, double qinv) {
   return r + l;
 }
 
+// x w mod q for x, w < q < 2^50 - 2^10 given wq = w/q: the exact value of
+// x w - c q with c the rounded quotient, in (-7/8 q, 7/8 q).
+NTT_HD double f64_mulmod_pre(double x, double w, double wq, double q) {
+  const double h = x * w;
+  const double l = fma_rn(x, w, -h);
+  const double c = rint_rn(x * wq);
+  return fma_rn(-c, q, h) + l;
+}
+
+// The ModDown step on a reduced sum r in [0, p): (x - r) s mod p for the
+// residue x in [0, p), with s < p < 2^50 - 2^10 and sq = s / p.  |x - r| < p,
+// so the product is exact as for non-negative operands.
+NTT_HD double f64_sub_scale(double x, double r, double s, double sq, double p) {
+  const double v = f64_mulmod_pre(x - r, s, sq, p);
+  return v < 0.0 ? v + p : v;
+}
+
 // General product of two lazily-reduced operands (neither is a table entry).
 NTT_HD double f64_mulmod2(double x, double y, double q, double qinv) {
   return f64_mulmod(x, y, q, qinv);
@@ -110,17 +144,16 @@ NTT_HD double f64_canon(double x, double q, double qinv) {
   return r;
 }
 
-// Shoup: y*w mod q in [0, 2q) for any y < 2^64, q < 2^63.  On the device from
-// 32-bit halves, with nq = 2^64 - q accumulated into the low product: the two
+// Shoup: y*w mod q in [0, 2q) for any y < 2^64, q < 2^63.  From 32-bit
+// halves, with nq = 2^64 - q accumulated into the low product: the two
 // low halves share one multiply-add chain and no 64-bit subtraction (with its
 // carry through a mask register) follows.  With the sign selects below a
 // butterfly of the forward rows went from 66 to 58 instructions and from seven
 // wait states to two; products of 3 x 11 limbs of 2^14 at 60 bits 42.1 -> 37.8 us.
 NTT_HD uint64_t shoup_mul_n(uint64_t y, uint64_t w, uint64_t ws, uint64_t nq) {
-#ifdef __HIP_DEVICE_COMPILE__
   const uint32_t yl = (uint32_t)y, yh = (uint32_t)(y >> 32);
   const uint32_t sl = (uint32_t)ws, sh = (uint32_t)(ws >> 32);
-  const uint64_t t1 = (uint64_t)yl * sh + __umulhi(yl, sl);
+  const uint64_t t1 = (uint64_t)yl * sh + mulhi32(yl, sl);
   const uint64_t t2 = (uint64_t)yh * sl + (uint32_t)t1;
   const uint64_t h = (uint64_t)yh * sh + (t1 >> 32) + (t2 >> 32);
   const uint32_t hl = (uint32_t)h, hh = (uint32_t)(h >> 32);
@@ -129,9 +162,6 @@ NTT_HD uint64_t shoup_mul_n(uint64_t y, uint64_t w, uint64_t ws, uint64_t nq) {
   const uint32_t hi = (uint32_t)(acc >> 32) + yl * (uint32_t)(w >> 32) + yh * (uint32_t)w +
                       hl * nh + hh * nl;
   return ((uint64_t)hi << 32) | (uint32_t)acc;
-#else
-  return y * w + mulhi64(y, ws) * nq;
-#endif
 }
 NTT_HD uint64_t shoup_mul(uint64_t y, uint64_t w, uint64_t ws, uint64_t q) {
   return shoup_mul_n(y, w, ws, 0 - q);
@@ -144,20 +174,15 @@ NTT_HD uint64_t cond_sub_n(uint64_t x, uint64_t nm) {
   return (int64_t)d < 0 ? x : d;
 }
 
-// Low 64 bits of (hi 2^64 + lo) >> s, s = 0 .. 63, on the device from 32-bit funnel
-// shifts: a 64-bit vector shift whose amount sits in the highest register of the
-// wave's allocation gave wrong words on gfx950 once several workgroups shared a
-// compute unit (a pointwise kernel with the amount in v39 of 40 registers), and
-// which register the compiler picks cannot be chosen here.
+// Low 64 bits of (hi 2^64 + lo) >> s, s = 0 .. 63, from 32-bit funnel shifts: a
+// pointwise kernel with a 64-bit vector shift whose amount lay in the last register of
+// the wave's allocation (v39 of 40) returned wrong words once several workgroups shared
+// a compute unit, and which register the compiler picks cannot be chosen in the source.
 NTT_HD uint64_t shr128(uint64_t lo, uint64_t hi, uint32_t s) {
-#ifdef __HIP_DEVICE_COMPILE__
   const uint32_t w0 = (uint32_t)lo, w1 = (uint32_t)(lo >> 32), w2 = (uint32_t)hi, w3 = (uint32_t)(hi >> 32);
   const bool up = s >= 32;
   const uint32_t x0 = up ? w1 : w0, x1 = up ? w2 : w1, x2 = up ? w3 : w2;
-  return ((uint64_t)__builtin_amdgcn_alignbit(x2, x1, s) << 32) | __builtin_amdgcn_alignbit(x1, x0, s);
-#else
-  return s ? (lo >> s) | (hi << (64 - s)) : lo;
-#endif
+  return ((uint64_t)funnel32(x2, x1, s) << 32) | funnel32(x1, x0, s);
 }
 
 // Barrett-style product of two operands in [0, q), q < 2^62, b = bit length
@@ -196,6 +221,21 @@ struct LimbDev {
 struct TwI64 {
   uint64_t w, ws;
 };
+
+// The constants of modulus q that depend on its class alone.
+inline void set_limb_modulus(LimbDev& d, uint64_t q, uint32_t cls) {
+  d.q = q;
+  if (cls == 2) {
+    d.nq = 0 - q;
+    d.nq2 = 0 - 2 * q;
+  } else {
+    d.qd = (double)q;
+    d.qinv = 1.0 / (double)q;
+  }
+  d.cls = cls;
+  d.qbits = 64 - __builtin_clzll(q);
+  d.bmu = (uint64_t)(((unsigned __int128)1 << (2 * d.qbits)) / q);
+}
 
 // ---------------------------------------------------------------------------
 // Arithmetic classes used as kernel template parameters.
@@ -303,13 +343,13 @@ struct ArI64 {
   static constexpr bool kCenterRounds = false;
   uint64_t q, q2, nq, nq2, mu;
   uint32_t qbits;
+#if defined(__HIP_DEVICE_COMPILE__) || defined(NTT_LIMB_NEGATIONS)
+  // -q and -2q read, not formed here: a product with a visible negation is turned back
+  // into a product with q and a subtraction
   NTT_HD explicit ArI64(const LimbDev& d)
-      
-#ifdef __HIP_DEVICE_COMPILE__
-      // read, not formed here: a product with a visible negation is turned back into
-      // a product with q and a subtraction
       : q(d.q), q2(2 * d.q), nq(d.nq), nq2(d.nq2), mu(d.bmu), qbits(d.qbits) {}
 #else
+  NTT_HD explicit ArI64(const LimbDev& d)
       : q(d.q), q2(2 * d.q), nq(0 - d.q), nq2(0 - 2 * d.q), mu(d.bmu), qbits(d.qbits) {}
 #endif
   NTT_HD V from_word(W x) const { return x; }

@@ -102,17 +102,7 @@ static ntt_status build_plan(ntt_plan_s* p, const uint64_t* moduli) {
     const uint64_t ninvw = nt_mul(ninv, w1inv, q);
     LimbDev& d = limbs[l];
     std::memset(&d, 0, sizeof(d));
-    d.q = q;
-    if (c == 2) {
-      d.nq = 0 - q;
-      d.nq2 = 0 - 2 * q;
-    } else {
-      d.qd = (double)q;
-      d.qinv = 1.0 / (double)q;
-    }
-    d.cls = c;
-    d.qbits = 64 - __builtin_clzll(q);
-    d.bmu = (uint64_t)(((u128)1 << (2 * d.qbits)) / q);
+    set_limb_modulus(d, q, c);
     d.ninv_d = centred(ninv, q);
     d.ninvw_d = centred(ninvw, q);
     d.ninv = ninv;

@@ -177,7 +177,9 @@ NTT_HD uint64_t cond_sub_n(uint64_t x, uint64_t nm) {
 // Low 64 bits of (hi 2^64 + lo) >> s, s = 0 .. 63, from 32-bit funnel shifts: a
 // pointwise kernel with a 64-bit vector shift whose amount lay in the last register of
 // the wave's allocation (v39 of 40) returned wrong words once several workgroups shared
-// a compute unit, and which register the compiler picks cannot be chosen in the source.
+// a compute unit, and which register the compiler picks cannot be chosen in the source,
+// so no kernel shifts 64 bits by a vector register (test_device_code_host.py reads the
+// built code for it).
 NTT_HD uint64_t shr128(uint64_t lo, uint64_t hi, uint32_t s) {
   const uint32_t w0 = (uint32_t)lo, w1 = (uint32_t)(lo >> 32), w2 = (uint32_t)hi, w3 = (uint32_t)(hi >> 32);
   const bool up = s >= 32;

@@ -1,9 +1,14 @@
 """Host checks of the compiled kernels: the gfx950 code of the built library,
 disassembled.
 
+  * No 64-bit vector shift takes its amount from a vector register: one with its amount
+    in the last register of the wave's allocation returned wrong words (csrc/modarith.hpp,
+    shr128), and which register the compiler picks cannot be chosen in the source.
   * The kernels of the external product load, rotate and decompose their operands
     without divergent branches: a branch per element puts each load's latency after
-    the one before (a CMux step of 1000 ciphertexts of 2^8, 50-bit: 9.6 us so, 11.8 with branches).
+    the one before (a CMux step of 1000 ciphertexts of 2^8, 50-bit: 9.6 us so, 11.8
+    with branches).
+  * The matrix-core basis conversions keep their constants in registers.
 """
 import os
 import re
@@ -41,6 +46,16 @@ def kernels(objects):
             out.append((head.strip("<>:"), [ln.split("//")[0].strip() for ln in body]))
     assert len(out) > 500
     return out
+
+
+def test_no_64_bit_shift_by_a_vector_register(kernels):
+    shift = re.compile(r"v_(?:lshlrev_b64|lshrrev_b64|ashrrev_i64)\S* v\[\d+:\d+\], (v\d+),")
+    seen = 0
+    for name, body in kernels:
+        for ln in body:
+            seen += "rev_b64" in ln
+            assert not shift.match(ln), (name, ln)
+    assert seen > 1000  # shifts by constants and scalars: the pattern's mnemonics are the compiler's
 
 
 def test_external_product_operands_load_without_branches(kernels):

@@ -604,7 +604,8 @@ __global__ void __launch_bounds__(1024) bconv_ws_kernel(BconvArgs a) {
 
   // ---- helper waves: thread ht of 256 takes the coefficient pairs ht + 256 m
   // (pair index = limb * 16 + coefficient / 2), one 2-word load each.
-  typedef W W2 __attribute__((ext_vector_type(2)));
+  // (Aligned to one word only: callers' tensors may start at any.)
+  typedef W W2 __attribute__((ext_vector_type(2), aligned(sizeof(W))));
   const uint32_t ht = threadIdx.x - 64u * row_tiles;
   // Loads are unconditional, from indices clamped into the input (pairs past
   // the run or the limbs read valid words that the digit step ignores).

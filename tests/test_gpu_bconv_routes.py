@@ -63,3 +63,28 @@ def test_form_and_words(mode, L, M, batch, form, wb):
         assert took == (form if mfma is None else "matrix" if mfma else "vector")
         outs.append(out)
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("L,M", [(9, 5), (12, 20), (24, 3), (6, 5)])
+@pytest.mark.parametrize("wb", [32, 64])
+def test_operands_that_start_at_any_word(L, M, wb):
+    """Inputs and outputs one word past an allocation's start: the same words."""
+    pool = synth.primes_below(1 << (32 if wb == 32 else 50), 1 << 17, L + M)
+    src, dst = pool[:L], pool[L:]
+    n, batch = 1 << 12, 2
+    dt = torch.int32 if wb == 32 else torch.int64
+
+    def odd(rows):
+        return torch.zeros(batch * rows * n + 1, dtype=dt, device="cuda")[1:].view(batch, rows, n)
+
+    x = torch.stack([torch.randint(0, q, (batch, n), device="cuda").to(dt) for q in dst + src], dim=1)
+    conv, up = ntt.BasisConversion(n, src, dst, wb), ntt.BasisExtension(n, src, dst, wb)
+    down = ntt.BasisExtension(n, dst, src, wb)
+    s = x[:, M:].contiguous()
+    for call, inp, rows in ((conv, s, M), (up.mod_up, s, L + M), (down.mod_down, x, M)):
+        want, got, view = torch.empty((batch, rows, n), dtype=dt, device="cuda"), odd(rows), odd(inp.shape[1])
+        view.copy_(inp)
+        assert view.is_contiguous() and view.data_ptr() % (2 * wb // 8)
+        call(want, inp)
+        call(got, view)
+        assert torch.equal(got, want)

@@ -65,8 +65,8 @@ typedef enum {
  * N < 16 one column pass, N <= 2^12 one row pass, N = 2^16 rows of 2^12 words;
  * between, by arithmetic class (fp64: one pass at 2^13, over 64-bit words from 12
  * limb-rows on, and at 2^14 from 96 limb-rows on, else 2^12-word rows, 2^11 at
- * 2^15; 64-bit integers: 2^11-word rows).  Products choose theirs the same way.  Plans with NTT_FLAG_FUSED,
- * NTT_FLAG_ROW_RADIX8 or NTT_FLAG_ROW_RADIX4 keep 2^12-word rows above 2^12. */
+ * 2^15; 64-bit integers: 2^11-word rows).  Products choose theirs the same way.
+ * Plans with NTT_FLAG_FUSED, NTT_FLAG_ROW_RADIX8 or NTT_FLAG_ROW_RADIX4 keep 2^12-word rows above 2^12. */
 #define NTT_FLAG_SPLIT(n1) ((uint32_t)(((n1) + 1) & 0x1f) << 8)
 #define NTT_FLAG_SPLIT_MASK (0x1fu << 8)
 /* Force the 64-bit integer (Shoup) arithmetic for every limb, even where the
@@ -77,8 +77,9 @@ typedef enum {
  * tuning table chooses per direction and shape, else: radix-4 rows (below) for
  * the 64-bit integer class (q >= 2^50) when a call has at most 256 row chunks
  * (one per compute unit); otherwise radix-8 for inverse rows, forward rows of
- * 2^10 .. 2^11 words and polymul rows other than fp64 two-pass rows of 2^12
- * words or more, radix-16 for the rest. */
+ * 2^10 .. 2^11 words and product rows, except two-pass product rows of 2^12 words or
+ * more (fp64, and polymul over 64-bit integers from 32 limb-rows on), and radix-16 for
+ * the rest. */
 #define NTT_FLAG_ROW_RADIX8 (1u << 17)
 /* Two-pass transforms with 2^12-word rows (N = 2^13 .. 2^16) run both passes in
  * one persistent launch: the one global synchronisation per transform of the

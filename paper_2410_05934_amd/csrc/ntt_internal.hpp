@@ -173,18 +173,22 @@ inline uint32_t col_block_for(const ntt_plan_s* p, uint32_t batch) {
   return tuned_col_block(p->log_n, (uint32_t)dominant_class(p), (uint64_t)batch * p->L, 256u);
 }
 
-// Values per thread of product rows.  Measured (product / forward-and-multiply, us,
-// radix-8 against radix-16): 64-bit integers 3 x 11 limbs of 2^14 31 / 24 against
-// 36 / 28, 2 x 36 of 2^16 139 / 98 against 135 / 100; fp64 with rows up to 2^11 words
-// 4 limbs of 2^14 15 / 10 against 17 / 12, 144 43 / 33 against 44 / 35; fp64 with
-// 2^12-word rows 2 x 36 of 2^16 90 against 86.
-inline int polymul_rb_for(const ntt_plan_s* p, uint32_t split, uint32_t batch) {
+// Values per thread of product rows (inverse: polymul; else forward-and-multiply).
+// Measured (product / forward-and-multiply, us, radix-8 against radix-16): 64-bit
+// integers 3 x 11 limbs of 2^14 31 / 24 against 36 / 28; with 2^12-word rows 8 limbs of
+// 2^16 36 / 27 against 41 / 31, 24 54 / 38 against 58 / 42, 36 77 / 53 against 77 / 57, 72
+// 123 / 89 against 120 / 92, 144 239 / 166 against 223 / 172, so products take radix-16
+// there from 32 limb-rows on; fp64 with rows up to 2^11 words 4 limbs of 2^14 15 / 10
+// against 17 / 12, 144 43 / 33 against 44 / 35; fp64 with 2^12-word rows 2 x 36 of 2^16
+// 90 against 86.
+inline int polymul_rb_for(const ntt_plan_s* p, uint32_t split, uint32_t batch, bool inverse) {
   const int n2 = (int)p->log_n - (int)split;
   if (!row_rb_ok(3, n2)) return 4;
   if (p->row_rb == 3 || p->row_rb == 4) return p->row_rb;
   const int cls = dominant_class(p);
-  const uint32_t fallback = (split && cls != 2 && n2 > 11) ? 4u : 3u;
-  const int rb = (int)tuned_row_rb(4u, p->log_n, (uint32_t)cls, (uint64_t)batch * p->L, fallback);
+  const uint64_t rows = (uint64_t)batch * p->L;
+  const bool r16 = split && n2 > 11 && (cls != 2 || (inverse && rows >= 32));
+  const int rb = (int)tuned_row_rb(4u, p->log_n, (uint32_t)cls, rows, r16 ? 4u : 3u);
   return rb == 3 ? 3 : 4;
 }
 

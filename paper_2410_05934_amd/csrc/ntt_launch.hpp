@@ -354,7 +354,7 @@ template <class A>
 hipError_t polymul_cls(const ntt_plan_s* p, int c, void* out, const void* a, const void* b,
                        void* ws, uint32_t batch, uint32_t split, hipStream_t s) {
   const int n = p->log_n, n1 = (int)split, n2 = n - n1;
-  const int rb = polymul_rb_for(p, split, batch);
+  const int rb = polymul_rb_for(p, split, batch, true);
   hipError_t e;
   if (n1 == 0) {
     RowArgs ra = row_args(p, c, out, a, b, batch, n1);
@@ -392,7 +392,7 @@ hipError_t polymul_rows_cls(const ntt_plan_s* p, int c, const uint64_t* out_rows
                             uint32_t batch, uint32_t split, hipStream_t s) {
   const int n = p->log_n, n1 = (int)split, n2 = n - n1;
   if (n1 == 0 || n2 == 0) return hipErrorInvalidValue;
-  const int rb = polymul_rb_for(p, split, batch);
+  const int rb = polymul_rb_for(p, split, batch, true);
   hipError_t e;
   ColArgs ca = col_args(p, c, o, nullptr, batch, n1);
   ca.src_rows = a_rows;
@@ -412,7 +412,7 @@ template <class A>
 hipError_t fwdmul_cls(const ntt_plan_s* p, int c, void* out, void* a, void* b, uint32_t batch,
                       uint32_t split, hipStream_t s) {
   const int n = p->log_n, n1 = (int)split, n2 = n - n1;
-  const int rb = polymul_rb_for(p, split, batch);
+  const int rb = polymul_rb_for(p, split, batch, false);
   hipError_t e;
   if (n2 == 0 || n2 > 13) {
     // no paired rows for this split: two transforms and the product

@@ -102,3 +102,34 @@ def test_tuner_times_the_product_rows_that_calls_run(cls, logn, batch):
     finally:
         ntt.tune_clear()
     assert len(timed) == 2 and len(taken) == 1 and taken <= timed
+
+
+@pytest.mark.parametrize("rows,product,fwdmul", [(31, "polymul_row8", "fwdmul_row8"),
+                                                 (32, "polymul_row", "fwdmul_row8")])
+def test_wide_product_rows_of_2_12(rows, product, fwdmul):
+    """64-bit integers at 2^16: products take radix-16 rows from 32 limb-rows on,
+    forward-and-multiply radix-8; the words are those of a radix-8 plan."""
+    N, mods = 1 << 16, synth.primes_below(1 << 60, 1 << 17, 1)
+    draw = lambda: torch.randint(0, mods[0], (rows, 1, N), device="cuda")  # noqa: E731
+    a, b = draw(), draw()
+    got = []
+    for flags in (0, 1 << 17):
+        plan = ntt.Plan(N, mods, 64, flags)
+        c, m, u, v = torch.empty_like(a), torch.empty_like(a), a.clone(), b.clone()
+        ntt.stats_reset()
+        ntt.stats_enable(True)
+        try:
+            plan.polymul(c, a, b)
+            plan.forward_mul(m, u, v)
+            torch.cuda.synchronize()
+            names = {n.split("_fwd_")[0] for n in ntt.stats_collect()}
+        finally:
+            ntt.stats_enable(False)
+            ntt.stats_reset()
+        got.append((c, m))
+        if not flags:
+            assert product in names and fwdmul in names, names
+            assert not names & {"polymul_row", "polymul_row8", "fwdmul_row", "fwdmul_row8"} - {product, fwdmul}
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    one = to_host(a[:1], 64).astype(np.uint64), to_host(b[:1], 64).astype(np.uint64)
+    assert np.array_equal(to_host(got[0][0][:1], 64).astype(np.uint64), oracle.polymul(*one, mods))

@@ -63,10 +63,10 @@ typedef enum {
  * n1 = log2 N for N < 16).  Without it each call takes the split the tuning
  * table records for its shape (see ntt_tune_split), else the default:
  * N < 16 one column pass, N <= 2^12 one row pass, N = 2^16 rows of 2^12 words;
- * between, by arithmetic class (fp64: one pass at 2^13, over 64-bit words from 12
- * limb-rows on, and at 2^14 from 96 limb-rows on, else 2^12-word rows, 2^11 at
- * 2^15; 64-bit integers: 2^11-word rows).  Products choose theirs the same way.
- * Plans with NTT_FLAG_FUSED, NTT_FLAG_ROW_RADIX8 or NTT_FLAG_ROW_RADIX4 keep 2^12-word rows above 2^12. */
+ * between, by arithmetic class (fp64: one pass at 2^13, and at 2^14 from 96
+ * limb-rows on, else 2^12-word rows, 2^11 at 2^15; 64-bit integers: 2^11-word
+ * rows).  Products choose theirs the same way.  Plans with NTT_FLAG_FUSED,
+ * NTT_FLAG_ROW_RADIX8 or NTT_FLAG_ROW_RADIX4 keep 2^12-word rows above 2^12. */
 #define NTT_FLAG_SPLIT(n1) ((uint32_t)(((n1) + 1) & 0x1f) << 8)
 #define NTT_FLAG_SPLIT_MASK (0x1fu << 8)
 /* Force the 64-bit integer (Shoup) arithmetic for every limb, even where the

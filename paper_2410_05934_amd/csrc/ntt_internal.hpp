@@ -65,9 +65,9 @@ inline uint32_t split_4096(uint32_t log_n) {
   return log_n < 4 ? log_n : log_n <= 12 ? 0u : log_n - 12;
 }
 // Default column stages by arithmetic class.  Measured (forward / inverse, us):
-//   fp64 classes: N = 2^13 in one pass saves the second trip through memory (32
-//   limb-rows 9 / 9 against 12 / 11 with 2^12-word rows, 144: 10 / 10 against 17 / 17,
-//   324: 17 / 18 against 22 / 27; fewest rows: call_split); N = 2^15 with 2^11-word rows
+//   fp64 classes: N = 2^13 in one pass saves the second trip through memory at any
+//   batch (32 limb-rows 9 / 9 against 12 / 11 with 2^12-word rows, 144: 10 / 10
+//   against 17 / 17, 324: 17 / 18 against 22 / 27); N = 2^15 with 2^11-word rows
 //   (36 limb-rows 17 / 17 against 18 / 19).
 //   64-bit integers: 2^11-word rows up to N = 2^15 (144 limb-rows of 2^14: 25 / 32
 //   against 29 / 33; of 2^15 42 / 45 against 44 / 45), since its long butterflies
@@ -246,18 +246,12 @@ inline bool xprod_fits(const ntt_plan_s* p, XpKind kind, uint32_t rows, uint32_t
 // runs in one pass (a workgroup of 139 KB of LDS per compute unit) when there are
 // enough limb-rows to fill the chip with them (forward / inverse, us, against two
 // passes: 144 rows 16 / 18 and 22 / 26, 324 rows 31 / 34 and 35 / 38, 36 rows 14 / 15
-// and 13 / 13).  N = 2^13 over fp64 moduli in 64-bit words takes two passes below 12
-// limb-rows, where its single pass leaves a compute unit a longer chain and no second
-// trip is saved (device time: 1 row 7.5 / 7.0 two passes, 7.9 / 8.0 one, 8 rows 7.9 /
-// 7.3 and 8.1 / 8.2, 16 rows 8.8 / 7.7 and 8.1 / 8.3; in eager calls the line lies at
-// 8 to 12 rows both ways).
+// and 13 / 13).
 inline uint32_t call_split(const ntt_plan_s* p, uint32_t batch) {
   if (p->forced_split >= 0) return (uint32_t)p->forced_split;
   const uint32_t cls = (uint32_t)dominant_class(p);
   const uint64_t rows = (uint64_t)batch * p->L;
-  uint32_t fallback = p->log_n1;
-  if (p->size_split && p->log_n == 14 && cls != 2 && rows >= 96) fallback = 0;
-  if (p->size_split && p->log_n == 13 && cls == 1 && rows < 12) fallback = 1;
+  const uint32_t fallback = p->size_split && p->log_n == 14 && cls != 2 && rows >= 96 ? 0u : p->log_n1;
   return tuned_split_for(p->log_n, cls, rows, fallback);
 }
 

@@ -55,25 +55,6 @@ def test_default_split_gives_the_same_words(cls, logn, batch):
     assert np.array_equal(word(got["default"][1][-1:]), oracle.inverse(last, mods))
 
 
-@pytest.mark.parametrize("cls,rows,split", [("fp64", 1, 1), ("fp64", 11, 1), ("fp64", 12, 0),
-                                            ("u32", 1, 0), ("u32", 12, 0)])
-def test_few_rows_of_2_13(cls, rows, split):
-    """Two passes below 12 limb-rows of fp64 moduli in 64-bit words."""
-    bits, wb = PRIMES[cls]
-    N, dt = 1 << 13, torch.int32 if wb == 32 else torch.int64
-    mods = synth.primes_below(1 << bits, 1 << 17, 1)
-    plan = ntt.Plan(N, mods, wb)
-    assert plan.split_for(rows) == split
-    a = torch.randint(0, mods[0], (rows, 1, N), device="cuda").to(dt)
-    f, i = a.clone(), a.clone()
-    plan.forward(f)
-    plan.inverse(i)
-    torch.cuda.synchronize()
-    word = lambda t: to_host(t, wb).astype(np.uint64)  # noqa: E731
-    assert np.array_equal(word(f), oracle.forward(word(a), mods))
-    assert np.array_equal(word(i), oracle.inverse(word(a), mods))
-
-
 @pytest.mark.parametrize("cls,logn,batch", [("fp64", 14, 48), ("fp64", 13, 40), ("i64", 14, 2),
                                             ("fp64", 15, 2)])
 def test_tuner_times_the_product_rows_that_calls_run(cls, logn, batch):

@@ -65,10 +65,12 @@ inline uint32_t split_4096(uint32_t log_n) {
   return log_n < 4 ? log_n : log_n <= 12 ? 0u : log_n - 12;
 }
 // Default column stages by arithmetic class.  Measured (forward / inverse, us):
-//   fp64 classes: N = 2^13 in one pass saves the second trip through memory at any
-//   batch (32 limb-rows 9 / 9 against 12 / 11 with 2^12-word rows, 144: 10 / 10
-//   against 17 / 17, 324: 17 / 18 against 22 / 27); N = 2^15 with 2^11-word rows
-//   (36 limb-rows 17 / 17 against 18 / 19).
+//   fp64 classes: N = 2^13 in one pass saves the second trip through memory and a
+//   launch (32 limb-rows 9 / 9 against 12 / 11 with 2^12-word rows, 144: 10 / 10 against
+//   17 / 17, 324: 17 / 18 against 22 / 27; 1 row 7.8 / 7.9 against 8.5 / 8.3 and 8 rows
+//   8.1 / 8.2 against 9.0 / 8.6, though replayed from a graph, without the host's share,
+//   they take 7.9 / 8.0 against 7.5 / 7.0 and 8.1 / 8.2 against 7.9 / 7.3); N = 2^15 with
+//   2^11-word rows (36 limb-rows 17 / 17 against 18 / 19).
 //   64-bit integers: 2^11-word rows up to N = 2^15 (144 limb-rows of 2^14: 25 / 32
 //   against 29 / 33; of 2^15 42 / 45 against 44 / 45), since its long butterflies
 //   want more threads per transform; one pass at 2^13 is slower for few rows (3: 14

@@ -34,11 +34,13 @@ def _form(run):
     ("conv", 8, 4, 1, "vector"), ("conv", 9, 1, 1, "vector"), ("conv", 16, 2, 1, "matrix"),
     ("conv", 16, 2, 2, "vector"), ("conv", 9, 4, 3, "matrix"), ("conv", 9, 4, 4, "vector"),
     ("conv", 9, 5, 5, "matrix"), ("conv", 10, 8, 6, "vector"), ("conv", 10, 9, 6, "matrix"),
-    ("up", 11, 5, 6, "matrix"), ("conv", 17, 1, 8, "matrix"), ("up", 9, 4, 4, "vector"),
-    ("up", 9, 4, 3, "matrix"), ("down", 16, 8, 1, "matrix"), ("down", 16, 8, 2, "vector"),
-    ("down", 12, 9, 8, "matrix"), ("down", 17, 4, 5, "matrix"), ("down", 17, 4, 6, "vector"),
-    ("down", 24, 2, 6, "vector"), ("down", 24, 3, 6, "matrix"), ("down", 25, 1, 6, "matrix"),
-    ("down", 37, 4, 6, "vector"), ("down", 37, 5, 6, "matrix")])
+    ("conv", 17, 1, 15, "matrix"), ("conv", 17, 2, 16, "vector"), ("conv", 21, 2, 16, "matrix"),
+    ("up", 10, 4, 4, "vector"), ("up", 10, 4, 3, "matrix"), ("up", 11, 4, 4, "matrix"),
+    ("up", 9, 5, 6, "matrix"), ("down", 16, 8, 1, "matrix"), ("down", 16, 8, 2, "vector"),
+    ("down", 12, 9, 7, "matrix"), ("down", 12, 9, 8, "vector"), ("down", 13, 9, 8, "matrix"),
+    ("down", 17, 4, 5, "matrix"), ("down", 17, 4, 6, "vector"), ("down", 24, 2, 6, "vector"),
+    ("down", 24, 3, 6, "matrix"), ("down", 25, 1, 6, "matrix"), ("down", 37, 4, 6, "vector"),
+    ("down", 37, 5, 6, "matrix")])
 @pytest.mark.parametrize("wb", [32, 64])
 def test_form_and_words(mode, L, M, batch, form, wb):
     """L source and M target moduli."""

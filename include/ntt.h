@@ -65,8 +65,10 @@ typedef enum {
  * N < 16 one column pass, N <= 2^12 one row pass, N = 2^16 rows of 2^12 words;
  * between, by arithmetic class (fp64: one pass at 2^13, and at 2^14 from 96
  * limb-rows on, else 2^12-word rows, 2^11 at 2^15; 64-bit integers: 2^11-word
- * rows).  Products choose theirs the same way.  Plans with NTT_FLAG_FUSED,
- * NTT_FLAG_ROW_RADIX8 or NTT_FLAG_ROW_RADIX4 keep 2^12-word rows above 2^12. */
+ * rows).  Products take the same splits except over fp64 moduli at 2^13 (one pass
+ * from 64 limb-rows on, else 2^10-word rows) and 2^14 (2^10-word rows: their rows are
+ * 2^13 words at most).  Plans with NTT_FLAG_FUSED, NTT_FLAG_ROW_RADIX8 or
+ * NTT_FLAG_ROW_RADIX4 keep 2^12-word rows above 2^12. */
 #define NTT_FLAG_SPLIT(n1) ((uint32_t)(((n1) + 1) & 0x1f) << 8)
 #define NTT_FLAG_SPLIT_MASK (0x1fu << 8)
 /* Force the 64-bit integer (Shoup) arithmetic for every limb, even where the
@@ -311,9 +313,9 @@ ntt_status ntt_external_product_decomposed(ntt_plan_t plan, void* out, const voi
  *   key   [comps * levels][comps][L][N], transform domain (the RGSW key)
  *   out   [num_ct][comps][L][N]; must not alias acc or key
  * Digit and size rules as ntt_external_product_decomposed.  One launch per class
- * (about the shapes ntt_external_product runs in one) rotates, decomposes, transforms, multiplies-and-accumulates,
- * inverse-transforms and adds; other shapes go through a stream-ordered
- * workspace. */
+ * (about the shapes ntt_external_product runs in one) rotates, decomposes, transforms,
+ * multiplies-and-accumulates, inverse-transforms and adds; other shapes go through a
+ * stream-ordered workspace. */
 ntt_status ntt_cmux(ntt_plan_t plan, void* out, const void* acc, const uint32_t* rot,
                     const void* key, uint32_t num_ct, uint32_t comps, uint32_t levels,
                     uint32_t log_base, void* stream);

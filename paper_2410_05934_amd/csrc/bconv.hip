@@ -246,10 +246,11 @@ __device__ __forceinline__ W f64_to_word(double r) {
 // ahead of the products.  The form above re-reads and re-forms every t_i for each
 // chunk of 8 targets and leaves a launch of one thread per coefficient with one
 // or two waves per SIMD, all of them waiting on scalar loads.  VALU work is some
-// 7 S + 25 operations per output, below the memory time up to about 10 sources.
-// Measured (ModDown, above form -> this): 36 + 4 limbs of 4 x 2^16 56.7 -> 35.6 us
-// (5.0 TB/s, the copy rate), 24 + 8 53.3 -> 32.6 us, 20 + 5 34.1 -> 21.2 us.
-
+// 7 S + 25 operations per output, so with more sources the products come to bound it
+// before memory does.  Measured (ModDown of 4 x 2^16 coefficients, rotating buffers,
+// above form -> this; a large copy runs at 4.7 to 4.9 TB/s here): 36 + 1 limbs 42.6 -> 32.3
+// us (4.7 TB/s), 36 + 4 57.6 -> 36.1 (4.4), 36 + 8 77.8 -> 41.4 (4.1), 24 + 8 54.6 -> 31.6
+// (3.7), 36 + 12 96.6 -> 50.3 (3.5).
 template <class W, int S, int MODE>
 __global__ void __launch_bounds__(kBconvBlock) bconv_few_kernel(BconvArgs a, uint32_t per) {
   const uint32_t gid = blockIdx.x * kBconvBlock + threadIdx.x;
@@ -450,7 +451,7 @@ __global__ void __launch_bounds__(256) bconv_mfma_kernel(BconvArgs a) {
 // the same time on each SIMD; one barrier per tile separates the buffers.
 // Measured on 36 -> 36 limbs of 4 x 2^16 coefficients: 57 us, against 151 us
 // for the streaming form above (bconv_mfma_kernel, which reloads the constant
-// operands per row tile); ModUp 61 us, ModDown 81-88 us.
+// operands per row tile); ModUp 61-64 us, ModDown 72-75 us.
 constexpr int kWsMaxTiles = 12;
 constexpr uint32_t kWsMaxLimbs = 48;  // 24 k-steps of constant operands in registers
 constexpr uint32_t kWsHelpers = 4;
@@ -522,10 +523,11 @@ __global__ void __launch_bounds__(1024) bconv_ws_kernel(BconvArgs a) {
     // tile ahead and so before the previous tile's stores: loads and stores
     // complete in order, and a load issued after them would wait for them.  For
     // the same reason s_J and s_J / p_J are held in registers, not read again per
-    // tile.  (us, loads at the start of the tile / so: 16 + 16 limbs of 4 x 2^16 25.1 /
-    // 21.5, 29 + 10 41.0 / 32.5, 36 + 36 60.6 / 55.7, 36 + 36 of 2 x 2^13 8.1 / 8.2.)
-    // With 24 k-steps the registers for it are not there (they spill: 48 + 48 limbs 109
-    // / 128), so that size loads at the start of the tile.
+    // tile.  (us, loads at the start of the tile / so, 4 x 2^16 coefficients over
+    // rotating buffers: 16 + 16 limbs 36.2 / 28.2, 24 + 24 58.4 / 48.4, 36 + 36 75.9 /
+    // 71.6; one set of buffers: 25.1 / 21.6, 46.5 / 38.0, 60.9 / 57.4; 36 + 36 of 2 x 2^13
+    // 8.1 / 8.2.)  With 24 k-steps the registers for it are not there (they spill: 48 + 48
+    // limbs 117 / 132), so that size loads at the start of the tile.
     auto load_sub = [&](uint32_t tile, W (&xs)[2]) {
       const uint64_t g = (uint64_t)tile * 32u + col;
 #pragma unroll
@@ -896,11 +898,12 @@ static ntt_status bconv_build(ntt_bconv_s** out, uint32_t N, const uint64_t* src
     if (e == hipSuccess) e = hipMemcpy(h->d_f2, f2.data(), f2.size() * 8, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(h->d_fp, fp.data(), fp.size() * 8, hipMemcpyHostToDevice);
   }
-  // Up to 8 sources the few-source vector form is at the memory rate; from 9 on
-  // its products cost more than the matrix cores' fixed work per output (us,
-  // vector / matrix: ModUp 8 -> 24 limbs of 4 x 2^16 24.0 / 24.7, 12 -> 12
-  // 23.7 / 18.4, 29 -> 10 79.8 / 37.8, 36 -> 1 45.9 / 37.2).  Without constants in
-  // registers (over 48 moduli) the matrix form needs 16 moduli on both sides.
+  // Up to 8 sources the few-source vector form is the faster one; from 9 on its products
+  // cost more than the matrix cores' fixed work per output, except where few targets or
+  // many coefficients say otherwise call by call (vector_first).  (us, vector / matrix:
+  // ModUp 8 -> 24 limbs of 4 x 2^16 24.0 / 24.7, 12 -> 12 23.7 / 18.4, 29 -> 10 79.8 /
+  // 37.8, 36 -> 1 45.9 / 37.2.)  Without constants in registers (over 48 moduli) the
+  // matrix form needs 16 moduli on both sides.
   const bool ws_shape = L <= kWsMaxLimbs && (M + 3) / 4 <= (uint32_t)kWsMaxTiles &&
                         !(flags & NTT_BCONV_NO_WS);
   h->mfma = h->f64 && N >= 32 && !(flags & NTT_BCONV_NO_MFMA) &&

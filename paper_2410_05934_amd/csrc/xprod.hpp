@@ -49,7 +49,7 @@ enum XpMode : int {
 // A digit goes into the transform as the small signed number it is (its residue mod
 // q gives the same words); the products take F as the forward leaves it (32-bit
 // moduli) or centred once when it is published, and are folded every eight rows.
-// CMux step of 342 ciphertexts at 2^10: 16.0 -> 15.3 us.
+// CMux step of 342 ciphertexts at 2^10: 16.0 -> 14.3 us.
 // kXpCmux: one CMux of blind rotation (Sec. II-B, Sec. IV-A): the digits are
 // those of X^r acc - acc (r = rot[grp]), and the stored result is acc plus the
 // inverse transform, i.e. acc + ExtProd(key, X^r acc - acc); cols = comps.
